@@ -130,10 +130,11 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out);
    uniform initial state with u_s inside the bodies.  Stream-ordered. */
 int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies, int32_t nbodies);
 
-/* Advance nsteps >= 0 steps (asynchronous on the stream).  Pairs of steps share one kernel launch
-   (the first kept on chip; see vplbm_steps_per_launch), an odd last step takes its own, and chunks
-   of 128 steps are replayed from a captured HIP graph (the environment variable
-   VPLBM_GRAPH_STEPS at create sets another even chunk; 0 launches every step directly).  Returns
+/* Advance nsteps >= 0 steps (asynchronous on the stream).  Several steps share one kernel launch, the
+   earlier ones kept on chip (see vplbm_steps_per_launch); what remains of a call takes launches of
+   fewer, and chunks of about 128 steps (whole launches) are replayed from a captured HIP graph (the
+   environment variable VPLBM_GRAPH_STEPS at create sets another even chunk; 0 launches every step
+   directly).  Returns
    VPLBM_EUNSTABLE if an earlier vplbm_observables saw status 1. */
 int vplbm_step(vplbm_sim s, int64_t nsteps);
 
@@ -199,12 +200,15 @@ int vplbm_momentum_exchange_noalloc(vplbm_sim s, double *out);
 int vplbm_steps_done(vplbm_sim s, int64_t *steps);
 int vplbm_stream(vplbm_sim s, void **stream);
 
-/* Lattice updates per kernel launch for this simulation: 3 for binary32 storage (the two
+/* Lattice updates per launch of the tiled kernels for this simulation: 3 for binary32 storage (the two
    intermediate steps kept on chip, 64 x 14 tiles; the convective outlet included), 2 for the
    other formats (pairs of steps, the intermediate one kept on chip), 1 when the environment variable
    VPLBM_TWO_STEP=0 was set at create; VPLBM_THREE_STEP=0 at create caps it at 2.  Moving bodies
    get a mask of their own for each intermediate step.  What remains of a call after its full
-   launches takes launches of one or two steps.  Every launch shape gives bitwise the same
+   launches takes launches of one or two steps.  Large lattices, unless one of the two variables
+   lowers the figure, take launches of more steps first (a strip sweep, the intermediate steps in
+   registers: six steps, four on smaller ones; VPLBM_STRIP=0 at create turns it off), and the tiled
+   kernels what remains.  Every launch shape gives bitwise the same
    populations (the update of Section 2 per node and step).  EINVAL: bad handle or NULL out. */
 int vplbm_steps_per_launch(vplbm_sim s, int32_t *steps);
 

@@ -8,14 +8,16 @@ hipcc cross-compiles without a GPU.  Packed-FP32 instructions are disabled on th
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libvplbm.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "runtime.hip", "pool.hip", "static_scratch.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "internal.hpp", "pool_policy.hpp", "step_plan.hpp", "static_scratch.hpp")] + [
+SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "runtime.hip", "pool.hip", "static_scratch.hip", "strip_f32.hip")]
+HEADERS = [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "internal.hpp", "pool_policy.hpp", "step_plan.hpp", "static_scratch.hpp", "reduce.hpp", "node.hpp", "strip.hpp", "strip_kernel.hpp", "strip_plan.hpp")] + [
     os.path.join(INCLUDE, "vplbm.h")]
 ARCH = os.environ.get("VPLBM_OFFLOAD_ARCH", "gfx950")
 # The probes: the step's access patterns with a trivial update, a copy, FMA chains (bench.py).
@@ -30,10 +32,10 @@ def hipcc():
     return path if os.path.exists(path) else "hipcc"
 
 
-def command(out=LIB, sources=None):
-    return [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+def command(out, sources, *flags):
+    return [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", *flags,
             "-munsafe-fp-atomics", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-            "-Wall", "-I", INCLUDE, "-I", CSRC, "-o", out] + (sources or SOURCES)
+            "-Wall", "-I", INCLUDE, "-I", CSRC, "-o", out] + sources
 
 
 def build(verbose: bool = False) -> str:
@@ -42,9 +44,7 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
-def _compile(lib, sources, verbose):
-    tmp = lib + ".tmp"
-    cmd = command(tmp, sources)
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -55,7 +55,16 @@ def _compile(lib, sources, verbose):
         raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
-    os.replace(tmp, lib)
+
+
+def _compile(lib, sources, verbose):
+    """Every source to an object of its own, side by side, then the library from the objects."""
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in sources]
+        with ThreadPoolExecutor(max_workers=max(1, min(len(sources), os.cpu_count() or 1))) as pool:
+            list(pool.map(lambda so: _run(command(so[1], [so[0]], "-c"), verbose), zip(sources, objs)))
+        _run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-o", lib + ".tmp"] + objs, verbose)
+    os.replace(lib + ".tmp", lib)
 
 
 def stale() -> bool:

@@ -9,72 +9,11 @@
 #include <stdlib.h>
 
 #include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace vplbm {
 
 // ---- the fused step --------------------------------------------------------------------------
-
-// Sub-slots [kSub][kRingWidth] of step t: one of kAccSets sets, used round-robin by step.
-__device__ __forceinline__ double *acc_set(const StepArgs &a, long long t)
-{
-    return a.acc + (size_t)(t & (kAccSets - 1)) * kSub * kRingWidth;
-}
-
-// Sum value q of the sub-slots of steps t - kMaxSteps .. t - 1 (those that exist) into their ring
-// entries, with one wave: lane l adds sub-slots l, l + 64, ... in order, then a fixed butterfly
-// adds the lanes, so a result does not depend on which workgroup folds or when.  One memory round
-// trip for all of them.  Nothing is cleared, so folding a step again gives the same value: a step
-// is folded by the next launch, and again by later ones while it is among their last kMaxSteps.
-// The fold always takes the shuffle form of the wave sum, so that every fold of a step (by any
-// kernel class, or by an observation) writes the same value.
-__device__ __forceinline__ void fold_recent(const StepArgs &a, long long t, int q)
-{
-    const int lane = threadIdx.x & 63;
-    double v[kMaxSteps];
-#pragma unroll
-    for (int d = 0; d < kMaxSteps; d++) v[d] = 0.0;
-    for (int b = lane; b < kSub; b += 64) {
-#pragma unroll
-        for (int d = 0; d < kMaxSteps; d++) v[d] += acc_set(a, t - 1 - d)[b * kRingWidth + q];
-    }
-#pragma unroll
-    for (int d = 0; d < kMaxSteps; d++) {
-        const double sum = wave_sum<false>(v[d]);
-        if (lane == 0 && t >= 1 + d) a.ring[(size_t)((t - 1 - d) % a.ring_len) * kRingWidth + q] = sum;
-    }
-}
-
-// Start of a launch that computes steps t .. t + n - 1 (1 <= n <= kMaxSteps): workgroup q's first
-// wave folds value q of steps t - kMaxSteps .. t - 1, and workgroup b zeroes sub-slot b of the
-// sets of steps t + n .. t + n + kMaxSteps - 1, which the next launch accumulates into.  The sets
-// one launch folds, writes and clears span at most 3 kMaxSteps consecutive steps, so with
-// kAccSets >= 3 kMaxSteps they are distinct.  Step s is first folded by a launch starting at most
-// kMaxSteps steps after s; the launch that clears its set for step s + kAccSets starts at least
-// kAccSets - 2 kMaxSteps + 1 steps after s, later in stream order, so every fold of s sees its
-// complete sums.
-__device__ __forceinline__ void reduction_prologue(const StepArgs &a, long long t, int n)
-{
-    if (threadIdx.x < 64)
-        for (int q = blockIdx.x; q < kRingWidth; q += gridDim.x) fold_recent(a, t, q);
-    if (threadIdx.x < kMaxSteps * kRingWidth) {
-        double *set = acc_set(a, t + n + threadIdx.x / kRingWidth);
-        const int q = threadIdx.x % kRingWidth;
-        for (int b = blockIdx.x; b < kSub; b += gridDim.x) set[b * kRingWidth + q] = 0.0;
-    }
-}
-
-// A workgroup's partial sums of step t (rows of per-wave partials, added in a fixed order) into
-// its sub-slot of the step's set: threads 0 .. kRingWidth - 1, after the barrier that completes
-// the rows.
-__device__ __forceinline__ void add_partials(const StepArgs &a, long long t, const double *rows, int nrows)
-{
-    if (threadIdx.x < kRingWidth) {
-        double v = 0.0;
-        for (int w = 0; w < nrows; w++) v += rows[w * kRingWidth + threadIdx.x];   // fixed order
-        double *slot = acc_set(a, t) + (blockIdx.x & (kSub - 1)) * kRingWidth;
-        if (v != 0.0) unsafeAtomicAdd(slot + threadIdx.x, v);
-    }
-}
 
 template <int S, bool NT>
 __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a)
@@ -88,11 +27,12 @@ __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a)
     __shared__ double wave_acc[kBlock / 64][kRingWidth];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long t = *a.t_base + a.t_off;
-    if (a.reduce) {
-        if (lane < kRingWidth) wave_acc[wave][lane] = 0.0;
-        reduction_prologue(a, t, 1);   // earlier steps' partials are complete (kernel boundary)
+    if ((int)blockIdx.x >= work_blocks(a)) {
+        fold_block(a, t, 1);           // earlier steps' partials are complete (kernel boundary)
+        return;
     }
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    if (a.reduce && lane < kRingWidth) wave_acc[wave][lane] = 0.0;
+    const int tile = xcd_tile(blockIdx.x, work_blocks(a));
     const int x = ((tile % a.ntx) << a.bx_log2) + (threadIdx.x & ((1 << a.bx_log2) - 1));
     const int y0 = (tile / a.ntx) * a.by * a.rows + (threadIdx.x >> a.bx_log2);
     const E *__restrict__ src = static_cast<const E *>(a.src);
@@ -160,15 +100,16 @@ __global__ __launch_bounds__(kBlock2) void step2_kernel(StepArgs a)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long t = *a.t_base + a.t_off;
     const Geom &g = a.g;
-    if (a.reduce) {
-        if (lane < kRingWidth) {
-            wave_acc[0][wave][lane] = 0.0;
-            wave_acc[1][wave][lane] = 0.0;
-        }
-        reduction_prologue(a, t, 2);
+    if ((int)blockIdx.x >= work_blocks(a)) {
+        fold_block(a, t, 2);
+        return;
+    }
+    if (a.reduce && lane < kRingWidth) {
+        wave_acc[0][wave][lane] = 0.0;
+        wave_acc[1][wave][lane] = 0.0;
     }
     const int ntx = (g.nx + TW - 1) / TW;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_tile(blockIdx.x, work_blocks(a));
     const int x0 = (tile % ntx) * TW, y0 = (tile / ntx) * TH;
     const E *__restrict__ src = static_cast<const E *>(a.src);
     E *__restrict__ dst = static_cast<E *>(a.dst);
@@ -243,7 +184,7 @@ __global__ __launch_bounds__(kBlock2) void step2_kernel(StepArgs a)
         double fx_d = 0.0, fy_d = 0.0;
         int id = 0;
         if ((x < g.nx) & (y < g.ny)) {
-            if constexpr (MF) id = *at(a.mask2, unsigned(y * g.pitch + x));
+            if constexpr (MF) id = *at(a.mask + a.mask_step, unsigned(y * g.pitch + x));
             T f[9];
             if (inner) pull_tile_shifts<S>(mid, EN, EW, x, y, x0, y0, f);
             else pull_tile<S>(mid, EN, EW, x, y, x0, y0, g, f);
@@ -259,8 +200,8 @@ __global__ __launch_bounds__(kBlock2) void step2_kernel(StepArgs a)
                 }
                 for (int k = 0; k < 3; k++) next[k * g.ny + y] = f[odirs[k]];
             }
-            const Macro<T> m = MF ? relax_node_id(f, id, a.bodies2, g, a.p, x, y)
-                                  : relax_node(f, a.mask2, a.bodies2, g, a.p, x, y, id);
+            const Macro<T> m = MF ? relax_node_id(f, id, a.bodies + a.state_step, g, a.p, x, y)
+                                  : relax_node(f, a.mask + a.mask_step, a.bodies + a.state_step, g, a.p, x, y, id);
             const unsigned i = y * g.pitch + x;
             store_node<S, NT>(dst, g.plane, i, f, i, (unsigned)(t + 1));
             const double rho_d = 1.0 + double(m.drho);
@@ -290,7 +231,7 @@ __global__ __launch_bounds__(kBlock2) void step2_kernel(StepArgs a)
 // of three one-step launches, with one read and one write of the planes per three updates.  A halo
 // position across a periodic edge holds the wrapped node; one beyond a non-periodic edge or a
 // ragged tile is skipped (no later pull reads it).  The phases take the masks and body states of
-// their own steps (a.mask, a.mask2, a.mask3).  CONV (an instantiation of its own): the lattice
+// their own steps (a.mask, a.mask + a.mask_step, a.mask + 2 * a.mask_step).  CONV (an instantiation of its own): the lattice
 // has a convective outlet; phase 1 reads the previous launch's records from global memory and
 // keeps the values it records at x = nx - 1 for the tile's rows and a one-row halo in LDS, phase 2
 // applies the outlet rule with them and keeps its own for the tile's rows, and phase 3 applies it
@@ -326,13 +267,14 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long t = *a.t_base + a.t_off;
     const Geom &g = a.g;
-    if (a.reduce) {
-        if (lane < kRingWidth)
-            for (int k = 0; k < 3; k++) wave_acc[k][wave][lane] = 0.0;
-        reduction_prologue(a, t, 3);
+    if ((int)blockIdx.x >= work_blocks(a)) {
+        fold_block(a, t, 3);
+        return;
     }
+    if (a.reduce && lane < kRingWidth)
+        for (int k = 0; k < 3; k++) wave_acc[k][wave][lane] = 0.0;
     const int ntx = (g.nx + TW - 1) / TW;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_tile(blockIdx.x, work_blocks(a));
     const int x0 = (tile % ntx) * TW, y0 = (tile / ntx) * TH;
     const E *__restrict__ src = static_cast<const E *>(a.src);
     // the source and destination planes as buffers (the host keeps three-step lattices below 4 GB)
@@ -419,7 +361,7 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
         double fx_d = 0.0, fy_d = 0.0;
         int id = 0;
         if (live) {
-            if constexpr (MF) id = *at(a.mask2, node[it]);
+            if constexpr (MF) id = *at(a.mask + a.mask_step, node[it]);
             if (inner) pull_tile_shifts<S, 2>(mid, EN, EW, ux, uy, x0, y0, res[it]);
             else pull_tile<S, 2>(mid, EN, EW, ux, uy, x0, y0, g, res[it]);
             if (CONV && !inner && x == g.nx - 1) {
@@ -434,8 +376,8 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
                 if (uy >= y0 && uy < y0 + TH)
                     for (int q = 0; q < 3; q++) outl2[q][uy - y0] = res[it][odirs[q]];
             }
-            const Macro<T> m = MF ? relax_node_id(res[it], id, a.bodies2, g, a.p, x, y)
-                                  : relax_node(res[it], a.mask2, a.bodies2, g, a.p, x, y, id);
+            const Macro<T> m = MF ? relax_node_id(res[it], id, a.bodies + a.state_step, g, a.p, x, y)
+                                  : relax_node(res[it], a.mask + a.mask_step, a.bodies + a.state_step, g, a.p, x, y, id);
             if (in_tile(ux, uy)) {
                 const double rho_d = 1.0 + double(m.drho);
                 mass += rho_d;
@@ -468,7 +410,7 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
         double fx_d = 0.0, fy_d = 0.0;
         int id = 0;
         if ((j < TW * TH) & (x < g.nx) & (y < g.ny)) {
-            if constexpr (MF) id = *at(a.mask3, unsigned(y * g.pitch + x));
+            if constexpr (MF) id = *at(a.mask + 2 * a.mask_step, unsigned(y * g.pitch + x));
             T f[9];
             if (inner) pull_tile_shifts<S, 2>(mid, EN, EW, x, y, x0, y0, f);
             else pull_tile<S, 2>(mid, EN, EW, x, y, x0, y0, g, f);
@@ -484,8 +426,8 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
                 }
                 for (int q = 0; q < 3; q++) next[q * g.ny + y] = f[odirs[q]];
             }
-            const Macro<T> m = MF ? relax_node_id(f, id, a.bodies3, g, a.p, x, y)
-                                  : relax_node(f, a.mask3, a.bodies3, g, a.p, x, y, id);
+            const Macro<T> m = MF ? relax_node_id(f, id, a.bodies + 2 * a.state_step, g, a.p, x, y)
+                                  : relax_node(f, a.mask + 2 * a.mask_step, a.bodies + 2 * a.state_step, g, a.p, x, y, id);
             store_node_buf<S, NT>(rdst, g.plane, y * g.pitch + x, f);
             const double rho_d = 1.0 + double(m.drho);
             mass += rho_d;
@@ -504,15 +446,11 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
     }
 }
 
-__global__ void fold_kernel(StepArgs a)
-{
-    const long long t = *a.t_base;
-    for (int q = 0; q < kRingWidth; q++) fold_recent(a, t, q);
-}
+__global__ void fold_kernel(StepArgs a) { fold_recent(a, *a.t_base, blockIdx.x); }
 
 hipError_t launch_fold(const StepArgs &a, hipStream_t st)
 {
-    fold_kernel<<<1, 64, 0, st>>>(a);
+    fold_kernel<<<kRingWidth, 64, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -545,7 +483,7 @@ TileShape tile_shape(int nx, int ny, int elem_bytes)
 
 hipError_t launch_step(int storage, const StepArgs &a, hipStream_t st)
 {
-    const dim3 grid(a.ntx * ((a.g.ny + a.by * a.rows - 1) / (a.by * a.rows))), block(kBlock);
+    const dim3 grid(all_blocks(a, a.ntx * ((a.g.ny + a.by * a.rows - 1) / (a.by * a.rows)))), block(kBlock);
 #define VPLBM_STEP(S)                                                                             \
     (a.nt_store ? step_kernel<S, true><<<grid, block, 0, st>>>(a)                                   \
                 : step_kernel<S, false><<<grid, block, 0, st>>>(a))
@@ -566,7 +504,7 @@ hipError_t launch_step(int storage, const StepArgs &a, hipStream_t st)
 template <int S, int TW, int TH>
 static void launch2(const StepArgs &a, hipStream_t st)
 {
-    const dim3 grid(((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH)), block(kBlock2);
+    const dim3 grid(all_blocks(a, ((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH))), block(kBlock2);
     if (a.outlet.prev) {
         if (a.nt_store) step2_kernel<S, TW, TH, true, true><<<grid, block, 0, st>>>(a);
         else step2_kernel<S, TW, TH, false, true><<<grid, block, 0, st>>>(a);
@@ -582,7 +520,7 @@ hipError_t launch_step3(int storage, const StepArgs &a, hipStream_t st)
 {
     constexpr int TW = 64, TH = 14;
     if (storage != kF32) return hipErrorInvalidValue;
-    const dim3 grid(((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH)), block(kBlock2);
+    const dim3 grid(all_blocks(a, ((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH))), block(kBlock2);
     if (a.outlet.prev) {   // convective outlet: an instantiation of its own
         if (a.nt_store) step3_kernel<kF32, TW, TH, true, true><<<grid, block, 0, st>>>(a);
         else step3_kernel<kF32, TW, TH, false, true><<<grid, block, 0, st>>>(a);

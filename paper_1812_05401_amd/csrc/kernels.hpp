@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "lattice.hpp"
+#include "strip_plan.hpp"
 
 namespace vplbm {
 
@@ -19,8 +20,8 @@ constexpr int kBlock2 = 512;                     // the two-step kernel's workgr
 // round-robin, so that a launch of up to kMaxSteps steps can fold the kMaxSteps steps before it
 // while it adds into its own and clears those of the next launch.
 constexpr int kSub = 64;
-constexpr int kMaxSteps = 3;                     // steps per launch, at most
-constexpr int kAccSets = 16;                     // >= 3 kMaxSteps, a power of two
+constexpr int kMaxSteps = 6;                     // steps per launch, at most
+constexpr int kAccSets = 32;                     // >= 3 kMaxSteps, a power of two
 static_assert(kAccSets >= 3 * kMaxSteps && (kAccSets & (kAccSets - 1)) == 0, "reduction sets");
 
 struct BodyParams {          // as given by the caller (vplbm_body), device copy
@@ -32,12 +33,10 @@ struct BodyParams {          // as given by the caller (vplbm_body), device copy
 struct StepArgs {
     const void *src;         // post-collision planes of the previous step
     void *dst;               // planes this step writes
-    const uint8_t *mask;     // body id per node (pitch = geometry pitch)
-    const BodyState *bodies; // body state at this step's time
-    const uint8_t *mask2;    // two- and three-step launches: mask and body states of the second
-    const BodyState *bodies2;//   step (the same arrays as mask / bodies unless bodies move)
-    const uint8_t *mask3;    // three-step launches: those of the third step
-    const BodyState *bodies3;
+    const uint8_t *mask;     // body id per node (pitch = geometry pitch) at the launch's first step
+    const BodyState *bodies; // body states at its time
+    size_t mask_step;        // from one step's mask and states to the next step's (0 unless bodies
+    int state_step;          //   move)
     double *ring;            // [ring_len][kRingWidth] per-step observables
     double *acc;             // [kAccSets][kSub][kRingWidth] per-step partial sums
     unsigned *status;        // bit 0: non-finite or non-positive density seen
@@ -61,12 +60,25 @@ TileShape tile_shape(int nx, int ny, int elem_bytes);
 
 hipError_t launch_step(int storage, const StepArgs &a, hipStream_t st);
 // Steps *t_base + t_off and the one after in one launch, from a.src into a.dst; the second step
-// takes its mask and body states from a.mask2 / a.bodies2 (the convective outlet included).
+// takes the next mask and body states (the convective outlet included).
 hipError_t launch_step2(int storage, const StepArgs &a, hipStream_t st);
 // Steps *t_base + t_off .. + 2 in one launch (binary32 storage, the convective outlet included);
-// the second and third steps take a.mask2 / a.bodies2 and a.mask3 / a.bodies3.
+// the second and third steps take the next masks and body states.
 bool step3_supported(int storage);
 hipError_t launch_step3(int storage, const StepArgs &a, hipStream_t st);
+
+// A form of the strip sweep: columns per lane, steps per launch, waves per SIMD, own columns of a
+// window and the halo beside them, and its launch: steps *t_base + t_off .. + steps - 1 over the device
+// table strips[n].
+struct StripShape {
+    int cols, steps, waves, own, halo;
+    void (*launch)(const StepArgs &a, const StripTile *strips, int n, hipStream_t st);
+};
+// Nodes from which the sweep is taken (below, a launch is a strip's latency: 0.9-1.08 times the tiled
+// kernels' speed at 512 x 512 to 1024 x 768, 1.1 at 1024 x 1024), and from which the form with two
+// columns per lane is (at 2048 x 1024 its strips are still too short).
+constexpr long long kStripLeast = 800000, kStripWide = 5LL << 19;
+const StripShape *strip_shape_f32(long long nodes);
 
 // Per-node density and penalized velocity of the current state into dense FP64 arrays.
 hipError_t launch_readback(int storage, const StepArgs &a, double *rho, double *ux, double *uy,

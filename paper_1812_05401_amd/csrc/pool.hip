@@ -1031,17 +1031,6 @@ int ensure_pool_graph(vplbm_pool p)
     return VPLBM_OK;
 }
 
-// Entry b of the device tile table: the tile that workgroup b of a launch over n tiles takes.
-// Workgroups are dealt to the 8 XCDs round-robin; each XCD takes one contiguous range of the
-// tiles (in simulation and tile order), so tiles that share cache lines through the x-shifted
-// pulls stay in one L2.  The kernels then read entry blockIdx.x directly.
-int xcd_entry(int b, int n)
-{
-    const int q = n >> 3, r = n & 7;
-    const int xcd = b & 7, j = b >> 3;
-    return xcd < r ? xcd * (q + 1) + j : r * (q + 1) + (xcd - r) * q + j;
-}
-
 int upload_tables(vplbm_pool p)
 {
     std::vector<TileRef> tiles;

@@ -13,6 +13,7 @@
 
 #include <mutex>
 #include <string>
+#include <vector>
 #include <unordered_set>
 
 #include "internal.hpp"
@@ -78,16 +79,27 @@ int elem_bytes(int storage)
 
 namespace {
 
-// Steps per captured graph replay.  128 (measured): 1.2% faster than 32 on the cache-resident
-// 2048 x 512 lattice, where the step-counter node and the gap between replays are a visible share
-// of a 22 us launch pair; no change on large lattices.  Calls of fewer steps are launched
-// directly.
-int graph_chunk()
+// Steps per captured graph replay, whole launches of `steps`.  About 128 (measured): 1.2% faster than
+// 32 on the cache-resident 2048 x 512 lattice, where the step-counter node and the gap between replays
+// are a visible share of a 22 us launch pair; no change on large lattices.  Calls of fewer steps are
+// launched directly.
+int graph_chunk(int steps)
 {
-    int k = 128;
+    int k = 128 / (2 * steps) * (2 * steps);
     if (const char *e = getenv("VPLBM_GRAPH_STEPS")) k = atoi(e);
     if (k < 0) k = 0;
     return k & ~1;   // even: a replay is whole two-step launches where those apply
+}
+
+// The strip sweep's form for a lattice of so many nodes.
+const StripShape *strip_shape(int storage, long long nodes)
+{
+    // tuning override: 0 the form of the largest lattices, 1 that of the smallest ones that take the sweep
+    if (const char *e = getenv("VPLBM_STRIP_SHAPE")) nodes = atoi(e) ? (storage == kF16SR || storage == kBF16SR ? kStripStochastic : kStripLeast) : 1LL << 30;
+    switch (storage) {
+    case kF32: return strip_shape_f32(nodes);
+    default: return nullptr;
+    }
 }
 
 }  // namespace
@@ -101,17 +113,21 @@ struct vplbm_sim_s {
     void *buf[2] = {nullptr, nullptr};
     int cur = 0;                         // buffer holding the current post-collision state
     uint8_t *mask = nullptr;
+    char *small = nullptr;               // the allocation that the small arrays below lie in
     BodyParams *d_params = nullptr;
     BodyState *d_state = nullptr;
-    uint8_t *mask_alt = nullptr;         // moving bodies: mask and body states of the first step of
-    BodyState *d_state_alt = nullptr;    //   a two- or three-step launch (mask / d_state take the last)
-    uint8_t *mask_alt2 = nullptr;        //   and of the second step of a three-step launch
-    BodyState *d_state_alt2 = nullptr;
+    // Moving bodies: mask_all holds a mask for each step of a launch, the last of which is `mask`, so a
+    // launch of k steps takes the last k; without, mask_all is `mask` alone.  d_state_all likewise.
+    uint8_t *mask_all = nullptr;
+    BodyState *d_state_all = nullptr;
+    int nmasks = 1;
     BodyParams h_params[kMaxBodies];
     int nbodies = 0;
     bool device_mask = false;
     bool moving = false;
     int env_box[kMaxBodies][4];          // x0, y0, w, h swept by each moving body
+    int solid_box[kMaxBodies][4];        // boxes that hold every solid node at every time
+    int nsolid = 0;
     double *ring = nullptr;
     double *acc = nullptr;               // [kAccSets][kSub][kRingWidth] reduction sub-slots
     int ring_len = 0;
@@ -129,6 +145,10 @@ struct vplbm_sim_s {
     int graph_k = 0;
     bool two_step = true;                // two steps per launch where the case allows it
     bool three_step = true;              // three where the kernel exists for the case
+    bool strip = true;                   // four, by the strip sweep, where that exists
+    const StripShape *shape = nullptr;   // form of the strip sweep, if there is one
+    StripTile *strips = nullptr;         // device table of the sweep's strips (xcd_entry order)
+    int nstrips = 0, strip_cap = 0;      // 0: to be built (ensure_strips)
     int64_t steps = 0;
     bool unstable = false;
     NodeParams params{};
@@ -165,10 +185,8 @@ StepArgs step_args(vplbm_sim s, int src, int t_off)
     a.dst = s->buf[src ^ 1];
     a.mask = s->mask;
     a.bodies = s->d_state;
-    a.mask2 = s->mask;
-    a.bodies2 = s->d_state;
-    a.mask3 = s->mask;
-    a.bodies3 = s->d_state;
+    a.mask_step = 0;
+    a.state_step = 0;
     a.ring = s->ring;
     a.acc = s->acc;
     a.status = s->status;
@@ -189,7 +207,7 @@ StepArgs step_args(vplbm_sim s, int src, int t_off)
     return a;
 }
 
-// Body states and the swept part of the mask for the n (1 or 2) steps at *t_dev + t_off, ...
+// Body states and the swept part of the mask for the n (1 to kMaxSteps) steps at *t_dev + t_off, ...
 // (moving bodies), in one launch: step s into masks[s] / states[s] (the simulation's own, or for
 // the first step of a two-step launch the other mask and state array).
 hipError_t place_bodies_n(vplbm_sim s, int t_off, int n, hipStream_t st, uint8_t *const *masks,
@@ -235,7 +253,7 @@ hipError_t reset_outlet(vplbm_sim s)
 // Two steps per launch: moving bodies take a second mask for the first step.
 bool two_step_ok(vplbm_sim s)
 {
-    return s->two_step && (!s->moving || s->mask_alt);
+    return s->two_step && (!s->moving || s->nmasks >= 2);
 }
 
 // Three steps per launch: binary32 storage, planes below 4 GB (the kernel stores through a 32-bit
@@ -243,63 +261,129 @@ bool two_step_ok(vplbm_sim s)
 bool three_step_ok(vplbm_sim s)
 {
     return s->three_step && two_step_ok(s) && step3_supported(s->storage) &&
-           s->buf_bytes <= 0xFFFFFFFFu && (!s->moving || s->mask_alt2);
+           s->buf_bytes <= 0xFFFFFFFFu && (!s->moving || s->nmasks >= 3);
 }
 
-// Enqueue n steps starting from the state in buf[first_src]: triples of steps in three-step
-// launches where the case allows them (unless VPLBM_THREE_STEP=0 turned them off), else pairs in
-// two-step launches (unless VPLBM_TWO_STEP=0), and what remains one or two at a time.  Every
-// launch moves the state to the other buffer; *flip is the parity of the number of launches.
+// Steps per launch of the strip sweep for this simulation, 0: not taken.  Its buffer resources hold
+// 32-bit sizes, and a row of a periodic lattice wraps once at most.
+int strip_k(vplbm_sim s)
+{
+    const int k = s->shape ? s->shape->steps : 0;
+    const bool ok = k && s->strip && s->two_step && s->three_step && s->buf_bytes <= 0xFFFFFFFFu &&
+                    s->g.ny >= k && (!s->moving || s->nmasks >= k);
+    return ok ? k : 0;
+}
+
+// Enqueue n steps starting from the state in buf[first_src]: as many as a launch takes (see
+// vplbm_steps_per_launch), and what remains in launches of fewer.  Every launch moves the state to
+// the other buffer; *flip is the parity of the number of launches.
 hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int *flip)
 {
-    const bool two = two_step_ok(s);
-    const bool three = three_step_ok(s);
+    const int sweep = strip_k(s);
+    const int most = sweep ? sweep : three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1;
+    const size_t mask_bytes = (size_t)s->g.pitch * s->g.ny;
     int src = first_src;
     int j = 0;
     while (j < n) {
-        hipError_t e;
-        if (three && n - j >= 3) {
-            StepArgs a = step_args(s, src, j);
-            if (s->moving) {
-                // steps one and two on the other masks, the third on the simulation's own
-                uint8_t *m[3] = {s->mask_alt, s->mask_alt2, s->mask};
-                BodyState *b[3] = {s->d_state_alt, s->d_state_alt2, s->d_state};
-                e = place_bodies_n(s, j, 3, st, m, b);
-                if (e != hipSuccess) return e;
-                a.mask = s->mask_alt;
-                a.bodies = s->d_state_alt;
-                a.mask2 = s->mask_alt2;
-                a.bodies2 = s->d_state_alt2;
+        int k = n - j < most ? n - j : most;
+        if (k < sweep && k > 2) k = three_step_ok(s) ? 3 : 2;
+        StepArgs a = step_args(s, src, j);
+        hipError_t e = hipSuccess;
+        if (s->moving) {
+            // the last step on the simulation's own mask: after the launch it holds that step's
+            // bodies, as after one step per launch; the earlier ones on those before it
+            uint8_t *m[kMaxSteps];
+            BodyState *b[kMaxSteps];
+            for (int i = 0; i < k; i++) {
+                m[i] = s->mask - (k - 1 - i) * mask_bytes;
+                b[i] = s->d_state - (k - 1 - i) * kMaxBodies;
             }
-            e = launch_step3(s->storage, a, st);
-            j += 3;
-        } else if (two && n - j >= 2) {
-            StepArgs a = step_args(s, src, j);
-            if (s->moving) {
-                // the first step on the other mask, the second on the simulation's own: after
-                // the launch it holds the last step's bodies, as after one step per launch
-                uint8_t *m[2] = {s->mask_alt, s->mask};
-                BodyState *b[2] = {s->d_state_alt, s->d_state};
-                e = place_bodies_n(s, j, 2, st, m, b);
-                if (e != hipSuccess) return e;
-                a.mask = s->mask_alt;
-                a.bodies = s->d_state_alt;
-            }
-            e = launch_step2(s->storage, a, st);
-            j += 2;
-        } else {
-            if (s->moving) {
-                e = place_bodies(s, j, st);
-                if (e != hipSuccess) return e;
-            }
-            e = launch_step(s->storage, step_args(s, src, j), st);
-            j += 1;
+            e = place_bodies_n(s, j, k, st, m, b);
+            if (e != hipSuccess) return e;
+            a.mask = m[0];
+            a.bodies = b[0];
+            a.mask_step = mask_bytes;
+            a.state_step = kMaxBodies;
         }
+        if (k == sweep) {
+            s->shape->launch(a, s->strips, s->nstrips, st);
+            e = hipGetLastError();
+        }
+        else if (k == 3) e = launch_step3(s->storage, a, st);
+        else if (k == 2) e = launch_step2(s->storage, a, st);
+        else e = launch_step(s->storage, a, st);
         if (e != hipSuccess) return e;
+        j += k;
         src ^= 1;
     }
     *flip = src ^ first_src;
     return launch_advance(s->t_dev, n, st);
+}
+
+// Box of the nodes that body b may cover at any time, clipped to the lattice: 0 if there are none.
+int body_box(const Geom &g, const vplbm_body &b, int box[4])
+{
+    double ex = b.kind == VPLBM_RECT ? b.hx : b.r, ey = b.kind == VPLBM_RECT ? b.hy : b.r;
+    if (b.kind == VPLBM_DISK_OUTSIDE) ex = ey = INFINITY;
+    ex += fabs(b.ax) + 2.0;
+    ey += fabs(b.ay) + 2.0;
+    const double x0 = fmax(floor(b.cx - ex), 0.0), x1 = fmin(ceil(b.cx + ex), g.nx - 1.0);
+    const double y0 = fmax(floor(b.cy - ey), 0.0), y1 = fmin(ceil(b.cy + ey), g.ny - 1.0);
+    if (!(x1 >= x0 && y1 >= y0)) return 0;
+    box[0] = (int)x0;
+    box[1] = (int)y0;
+    box[2] = (int)(x1 - x0) + 1;
+    box[3] = (int)(y1 - y0) + 1;
+    return 1;
+}
+
+// Box of the solid nodes of a host mask: 0 if there are none.
+int mask_box(const Geom &g, const uint8_t *id, int box[4])
+{
+    int x0 = g.nx, x1 = -1, y0 = g.ny, y1 = -1;
+    for (int y = 0; y < g.ny; y++)
+        for (int x = 0; x < g.nx; x++)
+            if (id[(size_t)y * g.nx + x]) {
+                if (x < x0) x0 = x;
+                if (x > x1) x1 = x;
+                if (y < y0) y0 = y;
+                y1 = y;
+            }
+    if (x1 < 0) return 0;
+    box[0] = x0;
+    box[1] = y0;
+    box[2] = x1 - x0 + 1;
+    box[3] = y1 - y0 + 1;
+    return 1;
+}
+
+// The sweep's strips for the bodies that are set, in device memory: built before the first step on them.
+int ensure_strips(vplbm_sim s)
+{
+    if (!s->shape || s->nstrips) return VPLBM_OK;
+    const StripPlan plan{s->g.nx, s->g.ny, s->g.xper != 0, s->g.yper != 0, 64 * s->shape->cols, s->shape->halo, s->shape->steps,
+                         s->nsolid, s->solid_box};
+    int slots = strip_slots((long long)s->g.nx * s->g.ny, s->shape->own, 1024 * s->shape->waves);
+    if (const char *e = getenv("VPLBM_STRIP_SLOTS")) slots = atoi(e);   // tuning override
+    const std::vector<StripTile> list = plan_strips(plan, slots);
+    const int n = (int)list.size();
+    std::vector<StripTile> order(n);
+    for (int b = 0; b < n; b++) order[b] = list[xcd_entry(b, n)];
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    if (n > s->strip_cap) {
+        if (s->strips) HIP_TRY(hipFree(s->strips));
+        s->strips = nullptr;
+        s->strip_cap = 0;
+        if (hipMalloc(&s->strips, sizeof(StripTile) * n) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(VPLBM_ENOMEM, "cannot allocate the table of %d strips", n);
+        }
+        s->strip_cap = n;
+    }
+    HIP_TRY(hipMemcpyAsync(s->strips, order.data(), sizeof(StripTile) * n, hipMemcpyHostToDevice, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));   // the copy reads `order`
+    s->nstrips = n;
+    return VPLBM_OK;
 }
 
 int ensure_graph(vplbm_sim s, int parity)
@@ -341,9 +425,7 @@ void release(vplbm_sim s)
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (int p = 0; p < 2; p++)
         if (s->graph[p]) (void)hipGraphExecDestroy(s->graph[p]);
-    void *ptrs[] = {s->buf[0], s->buf[1], s->mask, s->mask_alt, s->mask_alt2, s->d_params, s->d_state,
-                    s->d_state_alt, s->d_state_alt2, s->ring, s->acc,
-                    s->status, s->t_dev, s->staging, s->outlet[0], s->outlet[1], s->snap, s->rpart};
+    void *ptrs[] = {s->buf[0], s->buf[1], s->mask_all, s->small, s->strips, s->staging, s->snap, s->rpart};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
@@ -452,7 +534,6 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     if (static_scratch_init() != VPLBM_OK) host_log("static scratch: %s", vplbm_last_error());
     s->storage = cfg->storage;
     s->ring_len = cfg->ring ? cfg->ring : 4096;
-    s->graph_k = graph_chunk();
     s->params = node_params(*cfg);
 
     Geom &g = s->g;
@@ -463,6 +544,8 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     g.xper = cfg->bc_xlo == VPLBM_PERIODIC;
     g.yper = cfg->bc_ylo == VPLBM_PERIODIC;
     g.inlet = cfg->bc_xlo == VPLBM_VELOCITY;
+    s->shape = strip_shape(cfg->storage, (long long)g.nx * g.ny);
+    s->graph_k = graph_chunk(s->shape ? s->shape->steps : 1);
     s->ts = tile_shape(g.nx, g.ny, elem_bytes(cfg->storage));
 
     if (cfg->stream) {
@@ -482,19 +565,24 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     if (const char *e = getenv("VPLBM_NT_STORE")) s->nt_store = atoi(e) ? 1 : 0;
     if (const char *e = getenv("VPLBM_TWO_STEP")) s->two_step = atoi(e) != 0;   // 0: one step per launch
     if (const char *e = getenv("VPLBM_THREE_STEP")) s->three_step = atoi(e) != 0; // 0: at most two
-    struct { void **p; size_t n; } allocs[] = {
-        {&s->buf[0], s->buf_bytes}, {&s->buf[1], s->buf_bytes},
-        {(void **)&s->mask, (size_t)g.pitch * g.ny},
+    if (const char *e = getenv("VPLBM_STRIP")) s->strip = atoi(e) != 0;           // 0: no strip sweep
+    // the small arrays share one allocation, zeroed at once; each starts at a multiple of 256 bytes
+    struct { void **p; size_t n; } smalls[] = {
         {(void **)&s->d_params, sizeof(BodyParams) * kMaxBodies},
-        {(void **)&s->d_state, sizeof(BodyState) * kMaxBodies},
-        {(void **)&s->d_state_alt, sizeof(BodyState) * kMaxBodies},
-        {(void **)&s->d_state_alt2, sizeof(BodyState) * kMaxBodies},
-        {(void **)&s->ring, sizeof(double) * kRingWidth * s->ring_len},
-        {(void **)&s->acc, sizeof(double) * kAccSets * kSub * kRingWidth},
+        {(void **)&s->d_state_all, sizeof(BodyState) * kMaxBodies * kMaxSteps},
         {(void **)&s->status, sizeof(unsigned) * 4},
         {(void **)&s->t_dev, sizeof(long long)},
+        {(void **)&s->acc, sizeof(double) * kAccSets * kSub * kRingWidth},
+        {(void **)&s->ring, sizeof(double) * kRingWidth * s->ring_len},
         {&s->outlet[0], cfg->bc_xhi == VPLBM_CONVECTIVE ? sizeof(double) * 3 * g.ny : 0},
         {&s->outlet[1], cfg->bc_xhi == VPLBM_CONVECTIVE ? sizeof(double) * 3 * g.ny : 0},
+    };
+    size_t small_bytes = 0;
+    for (auto &a : smalls) small_bytes += (a.n + 255) / 256 * 256;
+    struct { void **p; size_t n; } allocs[] = {
+        {&s->buf[0], s->buf_bytes}, {&s->buf[1], s->buf_bytes},
+        {(void **)&s->mask_all, (size_t)g.pitch * g.ny},
+        {(void **)&s->small, small_bytes},
     };
     for (auto &a : allocs) {
         if (a.n == 0) continue;
@@ -505,15 +593,15 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
             return fail(VPLBM_ENOMEM, "cannot allocate %zu bytes of device memory", need);
         }
     }
+    size_t at = 0;
+    for (auto &a : smalls) {
+        if (a.n) *a.p = s->small + at;
+        at += (a.n + 255) / 256 * 256;
+    }
+    s->mask = s->mask_all;
+    s->d_state = s->d_state_all + (kMaxSteps - 1) * kMaxBodies;
     hipError_t e = hipMemsetAsync(s->mask, 0, (size_t)g.pitch * g.ny, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_state, 0, sizeof(BodyState) * kMaxBodies, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_state_alt, 0, sizeof(BodyState) * kMaxBodies, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_state_alt2, 0, sizeof(BodyState) * kMaxBodies, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_params, 0, sizeof(BodyParams) * kMaxBodies, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->ring, 0, sizeof(double) * kRingWidth * s->ring_len, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->acc, 0, sizeof(double) * kAccSets * kSub * kRingWidth, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->status, 0, sizeof(unsigned) * 4, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->t_dev, 0, sizeof(long long), s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(s->small, 0, small_bytes, s->stream);
     // Padding columns and the planes' tails are never read for results; clear them once.
     if (e == hipSuccess) e = hipMemsetAsync(s->buf[0], 0, s->buf_bytes, s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(s->buf[1], 0, s->buf_bytes, s->stream);
@@ -564,8 +652,11 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
             HIP_TRY(hipGraphExecDestroy(s->graph[p]));
             s->graph[p] = nullptr;
         }
+    int nsolid = 0, solid[kMaxBodies][4] = {};
+    if (body_id) nsolid = mask_box(g, body_id, solid[0]);
     for (int k = 0; k < nbodies; k++) {
         const vplbm_body &b = bodies[k];
+        if (!body_id) nsolid += body_box(g, b, solid[nsolid]);
         BodyParams &p = s->h_params[k];
         p.kind = b.kind; p.cx = b.cx; p.cy = b.cy; p.r = b.r; p.hx = b.hx; p.hy = b.hy;
         p.ux = b.ux; p.uy = b.uy; p.omega = b.omega; p.ax = b.ax; p.ay = b.ay; p.freq = b.freq;
@@ -589,23 +680,27 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
             }
         }
     }
-    // Moving bodies: the first step of a two-step launch takes a mask of its own, and so do the
-    // first two of a three-step launch.
-    if (moving && !s->mask_alt && hipMalloc(&s->mask_alt, (size_t)g.pitch * g.ny) != hipSuccess) {
-        (void)hipGetLastError();
-        s->mask_alt = nullptr;
-        return fail(VPLBM_ENOMEM, "cannot allocate the second mask (%zu bytes)", (size_t)g.pitch * g.ny);
+    // Moving bodies: every step of a launch takes a mask of its own.
+    const size_t mask_bytes = (size_t)g.pitch * g.ny;
+    if (moving && s->nmasks == 1) {
+        const bool sweep = s->strip && s->shape && s->two_step && s->three_step && s->buf_bytes <= 0xFFFFFFFFu;
+        const int want = sweep ? s->shape->steps : step3_supported(s->storage) ? 3 : 2;
+        uint8_t *m = nullptr;
+        if (hipMalloc(&m, want * mask_bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(VPLBM_ENOMEM, "cannot allocate %d masks (%zu bytes)", want, want * mask_bytes);
+        }
+        HIP_TRY(hipFree(s->mask_all));
+        s->mask_all = m;
+        s->mask = m + (want - 1) * mask_bytes;
+        s->nmasks = want;
     }
-    const bool third = moving && s->three_step && step3_supported(s->storage) &&
-                       s->buf_bytes <= 0xFFFFFFFFu;
-    if (third && !s->mask_alt2 && hipMalloc(&s->mask_alt2, (size_t)g.pitch * g.ny) != hipSuccess) {
-        (void)hipGetLastError();
-        s->mask_alt2 = nullptr;
-        return fail(VPLBM_ENOMEM, "cannot allocate the third mask (%zu bytes)", (size_t)g.pitch * g.ny);
-    }
+    s->nsolid = nsolid;
+    memcpy(s->solid_box, solid, sizeof solid);
     s->nbodies = nbodies;
     s->moving = moving;
     s->device_mask = body_id == nullptr;
+    s->nstrips = 0;
     if (nbodies) HIP_TRY(hipMemcpyAsync(s->d_params, s->h_params, sizeof(BodyParams) * nbodies, hipMemcpyHostToDevice, s->stream));
     HIP_TRY(launch_bodies(s->d_params, s->d_state, nbodies, s->t_dev, 0, s->stream));
     if (body_id) {
@@ -617,9 +712,8 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
         // The other masks: the whole lattice now; each launch of several steps then rebuilds
         // their swept boxes at the times of its first steps, and those of the simulation's own
         // at its last step's.
-        HIP_TRY(launch_mask(s->mask_alt, g, s->d_params, s->d_state, nbodies, 0, 0, g.nx, g.ny, s->stream));
-        if (s->mask_alt2)
-            HIP_TRY(launch_mask(s->mask_alt2, g, s->d_params, s->d_state, nbodies, 0, 0, g.nx, g.ny, s->stream));
+        for (uint8_t *m = s->mask_all; m < s->mask; m += mask_bytes)
+            HIP_TRY(launch_mask(m, g, s->d_params, s->d_state, nbodies, 0, 0, g.nx, g.ny, s->stream));
     }
     host_log("set_mask %p: %d bodies, moving %d, steps per launch %d", (void *)s, nbodies,
              moving ? 1 : 0, three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1);
@@ -636,6 +730,10 @@ int vplbm_step(vplbm_sim s, int64_t nsteps)
     if (!valid(s)) return fail(VPLBM_EINVAL, "invalid handle");
     if (nsteps < 0) return fail(VPLBM_EINVAL, "nsteps must be >= 0");
     if (s->unstable) return fail(VPLBM_EUNSTABLE, "the simulation became unstable (non-finite or non-positive density)");
+    if (nsteps > 0 && strip_k(s)) {
+        int rc = ensure_strips(s);
+        if (rc) return rc;
+    }
     while (nsteps > 0) {
         const StepChunk c = next_chunk(nsteps, s->graph_k);
         if (c.graph) {

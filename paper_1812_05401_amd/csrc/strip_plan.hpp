@@ -1,0 +1,115 @@
+// How a lattice is cut into the strips of a strip sweep (host only, no device code), kept apart from
+// the runtime so it can be checked on its own.
+#pragma once
+
+#include <algorithm>
+#include <vector>
+
+namespace vplbm {
+
+// A strip: its window's first own column, its rows y0 .. y1 - 1, and its form (StripForm).
+struct StripTile {
+    int x0, y0, y1, form;
+};
+enum StripForm { kPlain = 0, kMasked = 1, kEdge = 2 };
+
+struct StripPlan {
+    int nx, ny;
+    bool xper, yper;
+    int window, halo;        // columns of a window, and those on either side that are not its own
+    int steps;               // per launch
+    int nbox;                // boxes (x0, y0, w, h) that hold every solid node at every time
+    const int (*box)[4];
+};
+
+// Time of one row of a strip, relative to a plain one: rows that may hold solid nodes load ids and
+// may take the penalized collision; windows at an x edge load column by column.
+inline double strip_row_cost(int form) { return form == kPlain ? 1.0 : form == kMasked ? 2.0 : 1.4; }
+
+// The strips of a lattice, at most `slots` of them if that can be: every strip takes about the same
+// time, so that strips resident together end together.  Sorted by rows, then columns.
+inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
+{
+    struct Segment {
+        int x0, y0, y1, form;
+    };
+    std::vector<Segment> segs;
+    const int own = p.window - 2 * p.halo, reach = p.steps - 1;
+    std::vector<char> solid(p.ny);
+    for (int x0 = 0; x0 < p.nx; x0 += own) {
+        const int first = x0 - p.halo, last = first + p.window - 1;
+        if (first < 1 || last > p.nx - 2) {
+            segs.push_back({x0, 0, p.ny, kEdge});
+            continue;
+        }
+        // rows whose strip rows may see a solid node
+        std::fill(solid.begin(), solid.end(), 0);
+        for (int b = 0; b < p.nbox; b++) {
+            const int *q = p.box[b];
+            if (q[0] > last || q[0] + q[2] <= first) continue;
+            for (int y = q[1] - reach; y < q[1] + q[3] + reach; y++) {
+                if (y >= 0 && y < p.ny) solid[y] = 1;
+                else if (p.yper) solid[((y % p.ny) + p.ny) % p.ny] = 1;
+            }
+        }
+        for (int y = 0; y < p.ny;) {
+            int e = y + 1;
+            while (e < p.ny && solid[e] == solid[y]) e++;
+            segs.push_back({x0, y, e, solid[y] ? kMasked : kPlain});
+            y = e;
+        }
+    }
+    // Rows of a strip of one form within time t: its rows and those it computes beyond them.
+    auto rows = [&](double t, int form) {
+        const int r = (int)(t / strip_row_cost(form)) - 2 * reach;
+        return r < 1 ? 1 : r;
+    };
+    auto count = [&](double t) {
+        long long n = 0;
+        for (const Segment &s : segs) {
+            const int r = rows(t, s.form);
+            n += (s.y1 - s.y0 + r - 1) / r;
+        }
+        return n;
+    };
+    double lo = 2 * reach + 1, hi = 2.0 * (p.ny + 2 * reach + 1);
+    for (int i = 0; i < 40; i++) {
+        const double mid = 0.5 * (lo + hi);
+        if (count(mid) <= slots) hi = mid;
+        else lo = mid;
+    }
+    std::vector<StripTile> out;
+    for (const Segment &s : segs) {
+        const int r = rows(hi, s.form), h = s.y1 - s.y0, n = (h + r - 1) / r;
+        for (int i = 0; i < n; i++)
+            out.push_back({s.x0, s.y0 + (int)((long long)h * i / n), s.y0 + (int)((long long)h * (i + 1) / n), s.form});
+    }
+    std::stable_sort(out.begin(), out.end(), [](const StripTile &a, const StripTile &b) {
+        return a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0;
+    });
+    return out;
+}
+
+// Strips to cut a lattice into: as many rounds of the `resident` waves that the GPU holds at once as
+// leave a strip about 36 rows (measured at 8192 x 2048 and 8192 x 8192: fewer, taller strips end less
+// evenly, more compute too many rows twice), and one round of three quarters of them where that makes
+// strips of under eight rows.
+inline int strip_slots(long long nodes, int own, int resident)
+{
+    const double rounds = double(nodes) / own / 36.0 / resident;
+    if (rounds < 0.22) return resident * 3 / 4;
+    const int n = rounds < 0.4 ? 1 : (int)(rounds + 0.6);
+    return (int)std::min<long long>((long long)resident * 39 / 40 * n, 1 << 20);
+}
+
+// Entry of the sorted list that workgroup b of n takes: workgroups are dealt to the 8 XCDs
+// round-robin, and each XCD takes one contiguous range of the list, so that windows that share
+// cache lines stay in one L2.
+inline int xcd_entry(int b, int n)
+{
+    const int q = n >> 3, r = n & 7;
+    const int xcd = b & 7, j = b >> 3;
+    return xcd < r ? xcd * (q + 1) + j : r * (q + 1) + (xcd - r) * q + j;
+}
+
+}  // namespace vplbm
