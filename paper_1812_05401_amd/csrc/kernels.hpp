@@ -74,11 +74,14 @@ struct StripShape {
     int cols, steps, waves, own, halo;
     void (*launch)(const StepArgs &a, const StripTile *strips, int n, hipStream_t st);
 };
-// Nodes from which the sweep is taken (below, a launch is a strip's latency: 0.9-1.08 times the tiled
-// kernels' speed at 512 x 512 to 1024 x 768, 1.1 at 1024 x 1024), and from which the form with two
-// columns per lane is (at 2048 x 1024 its strips are still too short).
-constexpr long long kStripLeast = 800000, kStripWide = 5LL << 19;
+// Nodes from which the sweep is taken (below, a launch is a strip's latency: 0.72-1.08 times the tiled
+// kernels' speed at 512 x 512 to 1024 x 768, 1.08-1.17 at 1024 x 1024), and from which the form with two
+// columns per lane is (at 2048 x 1024 its strips are still too short).  The stochastically rounded
+// formats, whose random bits make a recomputed node dearer, gain from more (0.9 times at 4096 x 1024,
+// 1.17-1.27 at 8192 x 2048).
+constexpr long long kStripLeast = 800000, kStripWide = 5LL << 19, kStripStochastic = 6LL << 20;
 const StripShape *strip_shape_f32(long long nodes);
+const StripShape *strip_shape_f16(int storage, long long nodes);
 
 // Per-node density and penalized velocity of the current state into dense FP64 arrays.
 hipError_t launch_readback(int storage, const StepArgs &a, double *rho, double *ux, double *uy,

@@ -98,7 +98,9 @@ const StripShape *strip_shape(int storage, long long nodes)
     if (const char *e = getenv("VPLBM_STRIP_SHAPE")) nodes = atoi(e) ? (storage == kF16SR || storage == kBF16SR ? kStripStochastic : kStripLeast) : 1LL << 30;
     switch (storage) {
     case kF32: return strip_shape_f32(nodes);
-    default: return nullptr;
+    case kF64:
+    case kF32D: return nullptr;
+    default: return strip_shape_f16(storage, nodes);
     }
 }
 
