@@ -82,6 +82,7 @@ struct StripShape {
 constexpr long long kStripLeast = 800000, kStripWide = 5LL << 19, kStripStochastic = 6LL << 20;
 const StripShape *strip_shape_f32(long long nodes);
 const StripShape *strip_shape_f16(int storage, long long nodes);
+const StripShape *strip_shape_f64(int storage, long long nodes);
 
 // Per-node density and penalized velocity of the current state into dense FP64 arrays.
 hipError_t launch_readback(int storage, const StepArgs &a, double *rho, double *ux, double *uy,

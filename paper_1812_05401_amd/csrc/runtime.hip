@@ -99,7 +99,7 @@ const StripShape *strip_shape(int storage, long long nodes)
     switch (storage) {
     case kF32: return strip_shape_f32(nodes);
     case kF64:
-    case kF32D: return nullptr;
+    case kF32D: return strip_shape_f64(storage, nodes);
     default: return strip_shape_f16(storage, nodes);
     }
 }
