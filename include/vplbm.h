@@ -207,8 +207,9 @@ int vplbm_stream(vplbm_sim s, void **stream);
    get a mask of their own for each intermediate step.  What remains of a call after its full
    launches takes launches of one or two steps.  Large lattices, unless one of the two variables
    lowers the figure, take launches of more steps first (a strip sweep, the intermediate steps in
-   registers: six steps, four on smaller ones; VPLBM_STRIP=0 at create turns it off), and the tiled
-   kernels what remains.  Every launch shape gives bitwise the same
+   registers: three to six steps by format and size; VPLBM_STRIP=0 at create turns it off), and the
+   tiled kernels what remains.  Small ones take launches of up to eight steps on patches in LDS, the
+   remainder too (VPLBM_PATCH=0 at create turns that off).  Every launch shape gives bitwise the same
    populations (the update of Section 2 per node and step).  EINVAL: bad handle or NULL out. */
 int vplbm_steps_per_launch(vplbm_sim s, int32_t *steps);
 

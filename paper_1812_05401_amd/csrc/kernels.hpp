@@ -20,7 +20,7 @@ constexpr int kBlock2 = 512;                     // the two-step kernel's workgr
 // round-robin, so that a launch of up to kMaxSteps steps can fold the kMaxSteps steps before it
 // while it adds into its own and clears those of the next launch.
 constexpr int kSub = 64;
-constexpr int kMaxSteps = 6;                     // steps per launch, at most
+constexpr int kMaxSteps = 8;                     // steps per launch, at most
 constexpr int kAccSets = 32;                     // >= 3 kMaxSteps, a power of two
 static_assert(kAccSets >= 3 * kMaxSteps && (kAccSets & (kAccSets - 1)) == 0, "reduction sets");
 
@@ -66,6 +66,15 @@ hipError_t launch_step2(int storage, const StepArgs &a, hipStream_t st);
 // the second and third steps take the next masks and body states.
 bool step3_supported(int storage);
 hipError_t launch_step3(int storage, const StepArgs &a, hipStream_t st);
+
+// A form of the patch kernel (patch.hip): steps per launch at most, and its launch: steps
+// *t_base + t_off .. + nsteps - 1.  patch_shape: the one for a lattice of so many nodes, or nullptr where
+// another kernel is faster (most >= 0: where it has more nodes than that).
+struct PatchShape {
+    int steps;
+    void (*launch)(const StepArgs &a, int nsteps, hipStream_t st);
+};
+const PatchShape *patch_shape(int storage, long long nodes, long long most);
 
 // A form of the strip sweep: columns per lane, steps per launch, waves per SIMD, own columns of a
 // window and the halo beside them, and its launch: steps *t_base + t_off .. + steps - 1 over the device

@@ -150,6 +150,7 @@ struct vplbm_sim_s {
     bool strip = true;                   // four, by the strip sweep, where that exists
     const StripShape *shape = nullptr;   // form of the strip sweep, if there is one
     StripTile *strips = nullptr;         // device table of the sweep's strips (xcd_entry order)
+    const PatchShape *patch = nullptr;   // form of the patch kernel, if the lattice is small
     int nstrips = 0, strip_cap = 0;      // 0: to be built (ensure_strips)
     int64_t steps = 0;
     bool unstable = false;
@@ -276,13 +277,21 @@ int strip_k(vplbm_sim s)
     return ok ? k : 0;
 }
 
+// Steps per launch on patches in LDS, 0: not taken.
+int patch_k(vplbm_sim s)
+{
+    const bool ok = s->patch && s->two_step && s->three_step && (!s->moving || s->nmasks >= s->patch->steps);
+    return ok ? s->patch->steps : 0;
+}
+
 // Enqueue n steps starting from the state in buf[first_src]: as many as a launch takes (see
 // vplbm_steps_per_launch), and what remains in launches of fewer.  Every launch moves the state to
 // the other buffer; *flip is the parity of the number of launches.
 hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int *flip)
 {
     const int sweep = strip_k(s);
-    const int most = sweep ? sweep : three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1;
+    const int patch = patch_k(s);
+    const int most = patch ? patch : sweep ? sweep : three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1;
     const size_t mask_bytes = (size_t)s->g.pitch * s->g.ny;
     int src = first_src;
     int j = 0;
@@ -307,11 +316,13 @@ hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int 
             a.mask_step = mask_bytes;
             a.state_step = kMaxBodies;
         }
-        if (k == sweep) {
+        if (patch) {
+            s->patch->launch(a, k, st);
+            e = hipGetLastError();
+        } else if (k == sweep) {
             s->shape->launch(a, s->strips, s->nstrips, st);
             e = hipGetLastError();
-        }
-        else if (k == 3) e = launch_step3(s->storage, a, st);
+        } else if (k == 3) e = launch_step3(s->storage, a, st);
         else if (k == 2) e = launch_step2(s->storage, a, st);
         else e = launch_step(s->storage, a, st);
         if (e != hipSuccess) return e;
@@ -547,7 +558,10 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     g.yper = cfg->bc_ylo == VPLBM_PERIODIC;
     g.inlet = cfg->bc_xlo == VPLBM_VELOCITY;
     s->shape = strip_shape(cfg->storage, (long long)g.nx * g.ny);
-    s->graph_k = graph_chunk(s->shape ? s->shape->steps : 1);
+    long long patch_most = -1;
+    if (const char *e = getenv("VPLBM_PATCH")) patch_most = atoll(e);   // tuning: largest lattice in nodes, 0: none
+    s->patch = patch_shape(cfg->storage, (long long)g.nx * g.ny, patch_most);
+    s->graph_k = graph_chunk(s->patch ? s->patch->steps : s->shape ? s->shape->steps : 1);
     s->ts = tile_shape(g.nx, g.ny, elem_bytes(cfg->storage));
 
     if (cfg->stream) {
@@ -685,8 +699,8 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
     // Moving bodies: every step of a launch takes a mask of its own.
     const size_t mask_bytes = (size_t)g.pitch * g.ny;
     if (moving && s->nmasks == 1) {
-        const bool sweep = s->strip && s->shape && s->two_step && s->three_step && s->buf_bytes <= 0xFFFFFFFFu;
-        const int want = sweep ? s->shape->steps : step3_supported(s->storage) ? 3 : 2;
+        const bool many = s->two_step && s->three_step, sweep = many && s->strip && s->shape && s->buf_bytes <= 0xFFFFFFFFu;
+        const int want = many && s->patch ? s->patch->steps : sweep ? s->shape->steps : step3_supported(s->storage) ? 3 : 2;
         uint8_t *m = nullptr;
         if (hipMalloc(&m, want * mask_bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -732,7 +746,7 @@ int vplbm_step(vplbm_sim s, int64_t nsteps)
     if (!valid(s)) return fail(VPLBM_EINVAL, "invalid handle");
     if (nsteps < 0) return fail(VPLBM_EINVAL, "nsteps must be >= 0");
     if (s->unstable) return fail(VPLBM_EUNSTABLE, "the simulation became unstable (non-finite or non-positive density)");
-    if (nsteps > 0 && strip_k(s)) {
+    if (nsteps > 0 && !patch_k(s) && strip_k(s)) {
         int rc = ensure_strips(s);
         if (rc) return rc;
     }

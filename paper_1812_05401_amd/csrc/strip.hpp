@@ -126,6 +126,8 @@ template <int S, int C> struct Cols {
         p.v[C - 1] = lane_shift<kShl>(v[0]);
         return p;
     }
+    // the first column to element i of a plane
+    __device__ __forceinline__ void put(E *plane, unsigned i) const { *at(plane, i) = v[0]; }
     __device__ __forceinline__ T get(int c, T w) const { return Codec<S>::load(&v[c], 0, w); }
     __device__ __forceinline__ void set(int c, T h, T w) { Codec<S>::store(&v[c], 0, h, w); }
     __device__ __forceinline__ void take(int c, const Cols &o) { v[c] = o.v[c]; }
@@ -159,6 +161,8 @@ template <int S, int C> struct Cols16 {
         if constexpr (C == 2) __builtin_amdgcn_raw_buffer_store_b32(v, r, voff, soff, 0);
         else store1(r, voff, soff);
     }
+    // the first column to element i of a plane
+    __device__ __forceinline__ void put(E *plane, unsigned i) const { *at(plane, i) = __builtin_bit_cast(E, (unsigned short)v); }
     __device__ __forceinline__ unsigned left_() const
     {
         const unsigned n = lane_shift<kShr>(v);

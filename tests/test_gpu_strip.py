@@ -1,4 +1,4 @@
-"""The strip sweep against one step per launch: bitwise the same populations in every storage format,
+"""The strip sweep and the patches against one step per launch: bitwise the same populations in every storage format,
 over windows with and without x edges and solid nodes, strips of one row to all rows, remainders of
 every length and graph replays; the per-step sums agree up to summation order (1e-13 relative)."""
 import numpy as np
@@ -33,7 +33,7 @@ def pair(case, storage, fields, ids=None, **kw):
     """The same simulation with the strip sweep and with one step per launch."""
     out = []
     for strip in (1, 0):
-        with env(VPLBM_TWO_STEP=strip, VPLBM_THREE_STEP=strip, VPLBM_STRIP=strip, **{"VPLBM_STRIP_SHAPE": 0, **kw}):
+        with env(VPLBM_TWO_STEP=strip, VPLBM_THREE_STEP=strip, VPLBM_STRIP=strip, **{"VPLBM_STRIP_SHAPE": 0, "VPLBM_PATCH": 0, **kw}):
             s = gpu_sim(case, storage=storage, device_mask=ids is None)
             if ids is not None:
                 s.set_mask(ids, case.bodies)
@@ -60,6 +60,27 @@ def test_strip_sweep_bitwise_equals_one_step(gpu, spec, storage):
         same_run(a, b, 0, done, f"{spec} {storage} shape {shape} slots {slots}")
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("spec", LATTICES + [(157, 153, I.CHANNEL_CONVECTIVE, True), (301, 251, OPEN, True), (421, 331, CHANNEL, True),
+                                              (431, 400, OPEN, False)],
+                         ids=lambda s: f"{s[0]}x{s[1]}_{s[2][1]}_{s[2][2]}{'_moving' if s[3] else ''}")
+def test_patches_bitwise_equal_one_step(gpu, spec, storage):
+    """The lattices above and one of each larger patch size, launches of every number of steps."""
+    nx, ny, bc, moving = spec
+    u = (0.04, 0.0)
+    case = I.Case("patch", nx, ny, storage=storage, tau=0.6, bc=bc, u_in=u if bc[0] == I.VELOCITY else (0, 0),
+                  u0=u, bodies=bodies(nx, ny, moving) if ny > 20 else [])
+    a, b = pair(case, storage, I.random_fields(nx, ny, 6, u_mean=u), VPLBM_GRAPH_STEPS=16, VPLBM_PATCH=1000000)
+    done = 0
+    for n in (16, 1, 2, 3, 4, 5, 6, 7):
+        a.step(n)
+        b.step(n)
+        done += n
+    same_run(a, b, 0, done, f"{spec} {storage}")
+    a.close()
+    b.close()
 
 
 @pytest.mark.parametrize("storage", STORAGES)

@@ -187,6 +187,48 @@ def test_every_pull_reads_the_source_the_edge_rules_name(form, xper, yper):
             check(nx, ny, xper, yper, *form, rows)
 
 
+@pytest.mark.parametrize("xper,yper", itertools.product((True, False), repeat=2))
+@pytest.mark.parametrize("form,nsteps", [((8, 8, 8), 8), ((8, 8, 8), 3), ((16, 16, 6), 6), ((24, 16, 5), 5), ((24, 16, 5), 1),
+                                         ((16, 16, 4), 3), ((26, 18, 4), 4), ((20, 17, 3), 2)])
+def test_patch_pulls_read_the_source_the_edge_rules_name(form, nsteps, xper, yper):
+    """The patches of patch.hip: every LDS read of a step lies in the region, on a node that the step
+    before wrote, and is the source that edge_source names; every node is stored once."""
+    tw, th, top = form
+    ew, eh, skip = tw + 2 * (top - 1), th + 2 * (top - 1), top - nsteps
+    for nx, ny in [(3, 3), (5, 4), (21, 9), (40, 25), (33, 50)]:
+        stored = {}
+        for x0, y0 in itertools.product(range(0, nx, tw), range(0, ny, th)):
+            nodes = {}
+            for ex, ey in itertools.product(range(ew), range(eh)):
+                ux, uy = x0 + ex - (top - 1), y0 + ey - (top - 1)
+                if (xper or 0 <= ux < nx) and (yper or 0 <= uy < ny):
+                    nodes[ex, ey] = ux % nx, uy % ny, min(ex, ew - 1 - ex, ey, eh - 1 - ey)
+            mid = {}
+            for k in range(nsteps):
+                out = {}
+                for (ex, ey), (x, y, ring) in nodes.items():
+                    if ring < skip + k:
+                        continue
+                    plain = (xper or 0 < x < nx - 1) and (yper or 0 < y < ny - 1)
+                    ux, uy = x0 + ex - (top - 1), y0 + ey - (top - 1)
+                    for d in range(9):
+                        pa, sx, sy = edge_source(d, x, y, nx, ny, xper, yper)
+                        if k and not (not xper and x == 0 and CX[d] > 0):
+                            px, py, pd = ex - CX[d], ey - CY[d], d
+                            if not plain:
+                                if not yper and not 0 <= uy - CY[d] < ny:
+                                    py, pd = ey, MIRROR[d]
+                                if not xper and not 0 <= ux - CX[d] < nx:
+                                    px = ex
+                            assert mid[px, py] == (sx, sy) and pd == pa
+                    out[ex, ey] = x, y
+                    if k == nsteps - 1 and ring >= top - 1 and ux < nx and uy < ny:
+                        assert (x, y) not in stored
+                        stored[x, y] = 1
+                mid = out
+        assert len(stored) == nx * ny
+
+
 def test_reduction_sets_are_distinct_and_folded_before_cleared():
     """The reduction sets of reduce.hpp (kMaxSteps, kAccSets of kernels.hpp) over random mixes of
     launches of 1 to kMaxSteps steps, as tests/test_two_step_indexing.py has them for three."""
