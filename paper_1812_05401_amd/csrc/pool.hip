@@ -27,12 +27,16 @@
 #include <stddef.h>
 #include <string.h>
 
+#include <algorithm>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <unordered_set>
 #include <vector>
 
+#include "host_copy.hpp"
 #include "internal.hpp"
 #include "pool_policy.hpp"
 
@@ -687,7 +691,7 @@ struct Request {
     uint64_t bytes = 0;
     int64_t done = 0;
     vplbm_obs obs{};
-    std::vector<double> rho, ux, uy;
+    std::unique_ptr<double[]> fields;     // rho, ux, uy
     // device memory while resident
     void *buf[2] = {nullptr, nullptr};
     uint8_t *mask = nullptr;
@@ -732,6 +736,13 @@ std::unordered_set<const void *> g_pools;
 
 }  // namespace
 
+// A simulation out of its slot, its memory not yet released.
+struct Leaving {
+    int64_t id;
+    PoolSim sim;
+    int state;                            // its request's, once its fields are on the host
+};
+
 struct vplbm_pool_s {
     vplbm_pool_config cfg{};
     hipStream_t stream = nullptr;
@@ -748,6 +759,7 @@ struct vplbm_pool_s {
     long long *d_zero = nullptr;
     double *staging = nullptr;
     size_t staging_bytes = 0;
+    HostCopy host_copy;                   // results to host memory
     int tile_cap = 0;
     int ntiles = 0;
     long long t_host = 0;                 // host copy of *d_t after the last finished chunk
@@ -755,6 +767,8 @@ struct vplbm_pool_s {
     std::vector<int64_t> slot_req;        // request id per slot (-1 free)
     std::map<int64_t, Request> reqs;
     std::deque<int64_t> queue;
+    std::deque<Leaving> leaving;          // retired, in the order they are released
+    hipStream_t copy_stream = nullptr;    // their fields, beside the next replay
     int64_t next_id = 0;
     uint64_t used = 0;
     bool in_flight = false;
@@ -809,7 +823,8 @@ long long steps_done(const vplbm_pool p, const PoolSim &d)
     return n < d.target ? n : d.target;
 }
 
-// Copy a finished (or failed) simulation's results to the host and release its slot and memory.
+// Take a finished (or failed) simulation out of its slot: its observables and state.  Its memory stays
+// (release).  Launches and copies on the pool's stream, and waits for them.
 int retire(vplbm_pool p, int slot)
 {
     Request &r = p->reqs[p->slot_req[slot]];
@@ -827,47 +842,58 @@ int retire(vplbm_pool p, int slot)
         HIP_TRY(hipGetLastError());
         const char *dev_obs = reinterpret_cast<const char *>(p->d_sims + slot) + offsetof(PoolSim, obs);
         HIP_TRY(hipMemcpyAsync(d.obs, dev_obs, sizeof d.obs, hipMemcpyDeviceToHost, p->stream));
-    }
-    if (r.keep_fields) {
-        const size_t n = (size_t)d.g.nx * d.g.ny;
-        int rc = ensure_pool_staging(p, 3 * n * sizeof(double));
-        if (rc) return rc;
-        r.rho.resize(n);
-        r.ux.resize(n);
-        r.uy.resize(n);
-        StepArgs a{};
-        const int pb = pool_buf(done, d.spl, d.spk);
-        a.src = d.buf[pb];                          // the state after `done` steps
-        a.outlet.prev = d.conv ? d.outlet[pb] : nullptr;
-        a.outlet.u = d.ou;
-        a.mask = d.mask;
-        a.bodies = d.bodies;
-        a.t_base = p->d_zero;
-        a.g = d.g;
-        a.p = d.p;
-        HIP_TRY(launch_readback(d.storage, a, p->staging, p->staging + n, p->staging + 2 * n, p->stream));
-        HIP_TRY(hipMemcpyAsync(r.rho.data(), p->staging, n * sizeof(double), hipMemcpyDeviceToHost, p->stream));
-        HIP_TRY(hipMemcpyAsync(r.ux.data(), p->staging + n, n * sizeof(double), hipMemcpyDeviceToHost, p->stream));
-        HIP_TRY(hipMemcpyAsync(r.uy.data(), p->staging + 2 * n, n * sizeof(double), hipMemcpyDeviceToHost, p->stream));
-    }
-    HIP_TRY(hipStreamSynchronize(p->stream));
-    if (done == d.target) {
+        HIP_TRY(hipStreamSynchronize(p->stream));
         r.obs.mass = d.obs[0];
         for (int k = 0; k < kMaxBodies; k++) {
             r.obs.fx[k] = d.obs[1 + 2 * k];
             r.obs.fy[k] = d.obs[2 + 2 * k];
         }
     }
-    r.state = r.obs.status ? VPLBM_FAILED : (cancelled ? VPLBM_CANCELLED : VPLBM_DONE);
+    const int state = r.obs.status ? VPLBM_FAILED : (cancelled ? VPLBM_CANCELLED : VPLBM_DONE);
     host_log("pool %p: retire request %lld (%s) after %lld steps", (void *)p, (long long)r.id,
-        r.state == VPLBM_DONE ? "done" : r.state == VPLBM_FAILED ? "failed" : "cancelled", done);
-    free_request_memory(p, r);
-    p->used -= r.bytes;
+        state == VPLBM_DONE ? "done" : state == VPLBM_FAILED ? "failed" : "cancelled", done);
+    p->leaving.push_back({r.id, d, state});
     p->resident_nodes -= (uint64_t)r.cfg.nx * r.cfg.ny;
     r.slot = -1;
     p->slot_req[slot] = -1;
     memset(&p->h_sims[slot], 0, sizeof(PoolSim));
-    p->finished++;
+    return VPLBM_OK;
+}
+
+// The retired simulations' fields to the host, and their memory back.  st: the pool's stream, or one
+// beside it, after whatever touches their buffers or the staging memory has ended.
+int release(vplbm_pool p, hipStream_t st)
+{
+    while (!p->leaving.empty()) {
+        const Leaving &l = p->leaving.front();
+        Request &r = p->reqs[l.id];
+        const PoolSim &d = l.sim;
+        if (r.keep_fields) {
+            const size_t n = (size_t)d.g.nx * d.g.ny;
+            int rc = ensure_pool_staging(p, 3 * n * sizeof(double));
+            if (rc) return rc;
+            r.fields.reset(new (std::nothrow) double[3 * n]);
+            if (!r.fields) return fail(VPLBM_ENOMEM, "cannot allocate the host arrays of a result");
+            StepArgs a{};
+            const int pb = pool_buf(r.done, d.spl, d.spk);
+            a.src = d.buf[pb];                          // the state after the steps done
+            a.outlet.prev = d.conv ? d.outlet[pb] : nullptr;
+            a.outlet.u = d.ou;
+            a.mask = d.mask;
+            a.bodies = d.bodies;
+            a.t_base = p->d_zero;
+            a.g = d.g;
+            a.p = d.p;
+            HIP_TRY(launch_readback(d.storage, a, p->staging, p->staging + n, p->staging + 2 * n, st));
+            void *const dst[1] = {r.fields.get()};
+            HIP_TRY(p->host_copy.read(st, p->staging, 3 * n * sizeof(double), dst, 1));
+        }
+        free_request_memory(p, r);
+        p->used -= r.bytes;
+        p->finished++;
+        r.state = l.state;
+        p->leaving.pop_front();
+    }
     return VPLBM_OK;
 }
 
@@ -1160,9 +1186,9 @@ int vplbm_pool_submit(vplbm_pool p, const vplbm_config *cfg, const vplbm_body *b
     r.nsteps = nsteps;
     r.keep_fields = keep_fields ? 1 : 0;
     r.bytes = need;
-    p->reqs[r.id] = r;
-    p->queue.push_back(r.id);
     *id = r.id;
+    p->reqs[r.id] = std::move(r);
+    p->queue.push_back(*id);
     return VPLBM_OK;
 }
 
@@ -1227,7 +1253,7 @@ int vplbm_pool_residual(vplbm_pool p, int64_t id, double *residual)
     auto it = p->reqs.find(id);
     if (it == p->reqs.end()) return fail(VPLBM_EINVAL, "unknown request %lld", (long long)id);
     const Request &r = it->second;
-    *residual = r.state == VPLBM_RUNNING ? p->h_sims[r.slot].residual : r.residual;
+    *residual = r.slot >= 0 ? p->h_sims[r.slot].residual : r.residual;
     return VPLBM_OK;
 }
 
@@ -1251,6 +1277,20 @@ int vplbm_pool_advance(vplbm_pool p, int32_t *running, int32_t *queued, int32_t 
             if (rc) return rc;
             changed = true;
         }
+    }
+    // The retired simulations' fields take about 1 ms per 16 MB.  With requests waiting for the memory
+    // that comes first; with none it runs beside the next replay (a batch of 14 of 128 to 896 nodes
+    // square with fields: 9 of 74 ms).
+    const bool beside = p->queue.empty();
+    if (beside) {                         // no allocation while the replay runs: it would wait for it
+        size_t most = 0;
+        for (const Leaving &l : p->leaving)
+            if (p->reqs[l.id].keep_fields) most = std::max(most, 3 * (size_t)l.sim.g.nx * l.sim.g.ny * sizeof(double));
+        if (most && ensure_pool_staging(p, most) == VPLBM_OK && !p->copy_stream)
+            HIP_TRY(hipStreamCreateWithFlags(&p->copy_stream, hipStreamNonBlocking));
+    } else {
+        int rc = release(p, p->stream);
+        if (rc) return rc;
     }
     // First come, first served: the head of the queue waits for room rather than being passed.
     while (!p->queue.empty()) {
@@ -1299,6 +1339,10 @@ int vplbm_pool_advance(vplbm_pool p, int32_t *running, int32_t *queued, int32_t 
         HIP_TRY(hipGraphLaunch(p->graph, p->stream));
         p->in_flight = true;
     }
+    if (!p->leaving.empty()) {
+        int rc = release(p, p->copy_stream ? p->copy_stream : p->stream);
+        if (rc) return rc;
+    }
     if (running) *running = nrun;
     if (queued) *queued = (int32_t)p->queue.size();
     if (finished_total) *finished_total = p->finished;
@@ -1325,10 +1369,11 @@ int vplbm_pool_result(vplbm_pool p, int64_t id, vplbm_obs *out, double *rho, dou
         return fail(VPLBM_ESTATE, "request %lld has not finished", (long long)id);
     if ((rho || ux || uy) && !r.keep_fields) return fail(VPLBM_EINVAL, "request %lld did not keep its fields", (long long)id);
     if (out) *out = r.obs;
-    const size_t n = r.rho.size();
-    if (rho) memcpy(rho, r.rho.data(), n * sizeof(double));
-    if (ux) memcpy(ux, r.ux.data(), n * sizeof(double));
-    if (uy) memcpy(uy, r.uy.data(), n * sizeof(double));
+    const size_t n = (size_t)r.cfg.nx * r.cfg.ny;
+    const double *const field = r.fields.get();   // null: cancelled or refused before it ran
+    if (field && rho) host_copy(rho, field, n * sizeof(double));
+    if (field && ux) host_copy(ux, field + n, n * sizeof(double));
+    if (field && uy) host_copy(uy, field + 2 * n, n * sizeof(double));
     p->reqs.erase(it);
     return VPLBM_OK;
 }
@@ -1345,6 +1390,7 @@ int vplbm_pool_destroy(vplbm_pool p)
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
+    if (p->copy_stream) (void)hipStreamDestroy(p->copy_stream);
     if (p->own_stream) (void)hipStreamDestroy(p->stream);
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);

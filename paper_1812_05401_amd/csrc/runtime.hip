@@ -16,6 +16,7 @@
 #include <vector>
 #include <unordered_set>
 
+#include "host_copy.hpp"
 #include "internal.hpp"
 #include "kernels.hpp"
 #include "static_scratch.hpp"
@@ -138,6 +139,7 @@ struct vplbm_sim_s {
     double *staging = nullptr;          // dense FP64 host<->device staging
     void *outlet[2] = {nullptr, nullptr}; // convective outlet state per buffer parity
     size_t staging_bytes = 0;
+    HostCopy host_copy;                 // results to the caller's arrays
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int device = 0;                      // the device current at create (holds all the memory)
@@ -789,10 +791,12 @@ int vplbm_observables(vplbm_sim s, vplbm_obs *out, double *rho, double *ux, doub
     else
         memset(row, 0, sizeof row);
     HIP_TRY(hipMemcpyAsync(&status, s->status, sizeof status, hipMemcpyDeviceToHost, s->stream));
-    if (rho) HIP_TRY(hipMemcpyAsync(rho, s->staging, n * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    if (ux) HIP_TRY(hipMemcpyAsync(ux, s->staging + n, n * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    if (uy) HIP_TRY(hipMemcpyAsync(uy, s->staging + 2 * n, n * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
+    if (fields) {
+        void *const dst[3] = {rho, ux, uy};
+        HIP_TRY(s->host_copy.read(s->stream, s->staging, n * sizeof(double), dst, 3));
+    } else {
+        HIP_TRY(hipStreamSynchronize(s->stream));
+    }
     if (status & 1u) s->unstable = true;
     if (out) {
         memset(out, 0, sizeof *out);
@@ -831,8 +835,8 @@ int vplbm_get_populations(vplbm_sim s, double *pop)
     int rc = ensure_staging(s, 9 * n * sizeof(double));
     if (rc) return rc;
     HIP_TRY(launch_decode(s->storage, step_args(s, s->cur, 0), s->staging, s->stream));
-    HIP_TRY(hipMemcpyAsync(pop, s->staging, 9 * n * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
+    void *const dst[1] = {pop};
+    HIP_TRY(s->host_copy.read(s->stream, s->staging, 9 * n * sizeof(double), dst, 1));
     return VPLBM_OK;
 }
 
@@ -876,7 +880,8 @@ int vplbm_force_series(vplbm_sim s, int64_t first, int64_t count, double *out)
         const int64_t slot = (first + done) % s->ring_len;
         int64_t run = s->ring_len - slot;
         if (run > count - done) run = count - done;
-        HIP_TRY(hipMemcpyAsync(out + done * kRingWidth, s->ring + slot * kRingWidth, run * kRingWidth * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+        void *const dst[1] = {out + done * kRingWidth};
+        HIP_TRY(s->host_copy.read(s->stream, s->ring + slot * kRingWidth, run * kRingWidth * sizeof(double), dst, 1));
         done += run;
     }
     HIP_TRY(hipStreamSynchronize(s->stream));
