@@ -220,14 +220,14 @@ int vplbm_bytes_per_update(int32_t storage, int64_t *bytes);
 /* ---- serving pool -----------------------------------------------------------------------
  * Many independent simulations resident on one GPU at once, advanced together: every call to
  * vplbm_pool_advance replays one captured HIP graph of `steps_per_launch` steps of a batched
- * step kernel (three steps per launch for binary32 storage and two for the other formats, the
- * intermediate steps kept on chip, what remains of a replay last) with one
- * workgroup per tile of a device table spanning all resident simulations (each simulation's
- * per-node arithmetic is the single-simulation step's), then
+ * step kernel (two to five steps per launch by storage format, the intermediate steps kept on
+ * chip, what remains of a replay last) with one workgroup per entry, a tile or a strip, of a
+ * device table spanning all resident simulations (each simulation's per-node arithmetic is the
+ * single-simulation step's), then
  * retires the finished ones and admits queued requests, first come first served, while the
  * memory budget and the slots allow.  A simulation's results do not depend on what else is
  * resident: fields are bitwise identical alone and in a mix, and the final mass and body forces
- * are summed per tile in a fixed order.  Bodies must be static (no prescribed motion) and are
+ * are summed per tile or block of a strip in a fixed order.  Bodies must be static (no prescribed motion) and are
  * rasterized on the device.  Every edge condition of a single simulation is accepted, the
  * convective outlet included (its requests take the launches of their storage format).
  */

@@ -16,9 +16,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libvplbm.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "runtime.hip", "pool.hip", "static_scratch.hip", "host_copy.hip",
+SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "runtime.hip", "pool.hip", "pool_strip.hip", "pool_strip_f64.hip", "pool_patch.hip", "static_scratch.hip", "host_copy.hip",
                                             "strip_f32.hip", "strip_f16.hip", "strip_f64.hip", "patch.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "internal.hpp", "pool_policy.hpp", "step_plan.hpp", "static_scratch.hpp", "reduce.hpp", "node.hpp", "strip.hpp", "strip_kernel.hpp", "strip_plan.hpp",
+HEADERS = [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "internal.hpp", "pool.hpp", "pool_strip.hpp", "pool_job.hpp", "patch.hpp", "pool_policy.hpp", "step_plan.hpp", "static_scratch.hpp", "reduce.hpp", "node.hpp", "strip.hpp", "strip_kernel.hpp", "strip_plan.hpp",
                                             "host_copy.hpp")] + [
     os.path.join(INCLUDE, "vplbm.h")]
 ARCH = os.environ.get("VPLBM_OFFLOAD_ARCH", "gfx950")

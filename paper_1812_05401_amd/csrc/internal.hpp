@@ -23,5 +23,7 @@ int elem_bytes(int storage);
 int check_config(const vplbm_config *c);
 int check_bodies(const vplbm_body *b, int n);
 NodeParams node_params(const vplbm_config &c);
+// Box (x0, y0, w, h) of the nodes that body b may cover at any time, clipped to the lattice: 0 if there are none.
+int body_box(const Geom &g, const vplbm_body &b, int box[4]);
 
 }  // namespace vplbm

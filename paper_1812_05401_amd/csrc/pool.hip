@@ -1,21 +1,22 @@
 // Serving pool: many resident VP-LBM simulations advanced together by a batched step kernel
 // replayed from a captured HIP graph (see the pool section of include/vplbm.h).
 //
-// Device side.  A descriptor per slot (buffers, geometry, parameters, admission step, target) and
-// a table of tiles covering every resident simulation.  One workgroup per tile.  Binary32
-// simulations take three steps per launch on 64 x 14 tiles, the first two kept in LDS as in the
-// single-simulation three-step kernel; the other formats two steps per launch on 64 x 8 tiles, the
-// first kept in LDS as in the two-step kernel.  Each tile runs the same per-node update as the
-// single-simulation step, so a simulation's fields do not depend on its co-residents or on the
-// launch shape.  All resident simulations advance together, so a simulation's
-// steps done are the pool's step counter (on the device) minus its admission step: no per-step
-// bookkeeping launch is needed.  On a simulation's final step each tile writes its FP64 partial
-// sums (mass, body forces) to its own slot, summed in a fixed order inside the tile; at
-// retirement a fold kernel adds the tiles in tile order, so the final observables are bitwise
-// independent of the mix.
+// Device side.  A descriptor per slot (buffers, geometry, parameters, admission step, target) and for
+// every kernel a table that covers the resident simulations it advances, one entry per workgroup.  While
+// few nodes are resident these are patches in LDS (patch.hpp), three to five steps per launch, then the
+// strip sweep (strip.hpp), three to five steps too: see pool_choose.  f16sr between the two, and lattices
+// of very few rows or of planes beyond 4 GB, take two steps per launch on 64 x 8 tiles, the first kept
+// in LDS as in the two-step kernel.  All run the same per-node update as the single-simulation step, so
+// a simulation's fields do not depend on its co-residents or on the launch shape, and the kernel may
+// change at any replay boundary.  All resident simulations advance together, so a simulation's steps
+// done are the pool's step counter (on the device) minus its admission step: no per-step bookkeeping
+// launch is needed.  Whatever took the steps before, a simulation's last steps are taken by strips, block
+// by block (of those that have no strips, by tiles), and each block writes its FP64 partial sums of the
+// final step (mass, body forces) to its own place, summed in a fixed order; at retirement a fold kernel
+// adds them in order, so the final observables are bitwise independent of the mix.
 //
-// Early stop: for simulations that ask for it, the graph ends with a residual check (a per-tile
-// kernel and a per-slot fold) that lowers the simulation's target on the device once its
+// Early stop: for simulations that ask for it, the graph ends with a residual check (a kernel per entry
+// and a per-slot fold) that lowers the simulation's target on the device once its
 // velocity change is below the tolerance.
 //
 // Host side.  Between graph replays: retire finished, failed and cancelled simulations (fold,
@@ -38,61 +39,13 @@
 
 #include "host_copy.hpp"
 #include "internal.hpp"
+#include "pool.hpp"
 #include "pool_policy.hpp"
+#include "strip_plan.hpp"
 
 using namespace vplbm;
 
 namespace vplbm {
-
-constexpr int kPoolTileW = 64, kPoolTileH = 8;   // 512 nodes: one per thread of kBlock2
-constexpr int kPoolEW = kPoolTileW + 2, kPoolEN = kPoolEW * (kPoolTileH + 2);
-// binary32: three steps per launch on 64 x 14 tiles, an LDS tile with a two-node halo
-constexpr int kPool3H = 14;
-constexpr int kPool3EW = kPoolTileW + 4, kPool3EN = kPool3EW * (kPool3H + 4);
-constexpr int kPoolMaxSlots = 1024;
-static_assert(kPoolTileW * kPoolTileH == kBlock2, "one node per thread in the second step");
-
-struct PoolSim {
-    void *buf[2];
-    const uint8_t *mask;
-    const BodyState *bodies;
-    double *partials;        // [ntiles][kRingWidth] of the final step
-    Geom g;
-    NodeParams p;
-    int storage;
-    int ntx, ntiles;
-    int th;                  // tile height (the tile width is kPoolTileW)
-    int spk;                 // steps per kernel launch: 3 for binary32, else 2
-    int nt;                  // 1: non-temporal population stores (the resident buffers exceed the cache)
-    int conv;                // 1: convective outlet at x = nx - 1
-    double ou;               // its convection speed (the inlet speed)
-    void *outlet[2];         // its recorded values (3 x ny, compute type) per buffer parity
-    int active;
-    int spl;                 // steps per graph replay (the pool's steps_per_launch)
-    long long t0, target;    // pool step at admission; steps to run
-    unsigned status;
-    double obs[kRingWidth];  // folded final observables
-    // early stop (tol > 0): residual checks at done >= next_check, every `every` steps
-    double tol, residual;
-    long long every, next_check;
-    int have_snap;
-    double *snap;            // [2][ny*nx] velocity at the last check
-    double *rpart;           // [ntiles][2] residual partial sums
-};
-
-struct TileRef {
-    int slot, tile;
-};
-
-// Buffer holding a simulation's state after `done` steps.  Each graph replay of spl steps runs
-// ceil(spl / spk) launches of the simulation's kernel from the replay's start, spk steps each and
-// what remains last; a simulation is admitted at a replay boundary, and a launch moves its state
-// to the other buffer however many steps it takes (fewer when the simulation has fewer left).
-__host__ __device__ inline int pool_buf(long long done, int spl, int spk)
-{
-    const long long launches = (done / spl) * ((spl + spk - 1) / spk) + ((done % spl) + spk - 1) / spk;
-    return (int)(launches & 1);
-}
 
 // The final step's per-tile sums (mass, body forces): wave shuffles, then the waves in order,
 // into the tile's slot of the simulation's partials.  Called by every thread of the workgroup.
@@ -133,7 +86,7 @@ __device__ __forceinline__ void pool_tile_partials(const PoolSim &d, int tile, d
 // LDS (outl, 3 x kPoolTileH values), and the second applies the outlet rule with them and records
 // its own for the next launch.
 template <int S, bool CONV>
-__device__ __forceinline__ void pool_tile(const PoolSim &d, int tile, long long done, int nsteps,
+__device__ __forceinline__ void pool_tile(const PoolSim &d, int tile, long long done, int nsteps, int b,
                                           unsigned char *lds, double (*part)[kRingWidth],
                                           double *outl_lds, unsigned *status)
 {
@@ -142,7 +95,6 @@ __device__ __forceinline__ void pool_tile(const PoolSim &d, int tile, long long 
     using E = typename C::elem;
     constexpr int odirs[3] = {3, 6, 7};           // the directions entering from x = nx
     const Geom &g = d.g;
-    const int b = pool_buf(done, d.spl, d.spk);
     // selects rather than indexing: the kernel holds d in registers, not in memory
     const E *__restrict__ src = static_cast<const E *>(b ? d.buf[1] : d.buf[0]);
     E *__restrict__ dst = static_cast<E *>(b ? d.buf[0] : d.buf[1]);
@@ -225,330 +177,53 @@ __device__ __forceinline__ void pool_tile(const PoolSim &d, int tile, long long 
     if (done + nsteps == d.target) pool_tile_partials<wave_sum_dpp<T>()>(d, tile, rho, fx, fy, id, part);
 }
 
-// The lattice node at unwrapped position (ux, uy) of a tile, h or fewer nodes outside it: live
-// unless beyond a non-periodic edge or more than h beyond the lattice (a ragged tile); a position
-// across a periodic edge is the wrapped node.
-__device__ __forceinline__ bool pool_locate(const Geom &g, int ux, int uy, int h, int &x, int &y)
-{
-    x = ux;
-    y = uy;
-    if (x < 0 || x >= g.nx) {
-        if (g.xper && x >= -h && x < g.nx + h) x += x < 0 ? g.nx : -g.nx;
-        else return false;
-    }
-    if (y < 0 || y >= g.ny) {
-        if (g.yper && y >= -h && y < g.ny + h) y += y < 0 ? g.ny : -g.ny;
-        else return false;
-    }
-    return true;
-}
-
-// pull_interior_buf and store_node_buf (binary32) for the pool, with each plane's scalar offset
-// passed through readfirstlane.  The offsets are uniform over the workgroup (the simulation's
-// pitch and plane size); stated so, the compiler keeps them in scalar registers instead of
-// wrapping each buffer access in a loop over distinct lane values.
-__device__ __forceinline__ void pool_pull_buf(__amdgpu_buffer_rsrc_t r, unsigned plane, unsigned pitch,
-                                              unsigned i, float f[9])
-{
-    const int v = int(i * 4u);
-    const int P = int(pitch);
-    const int shift[9] = {0, -1, -P, 1, P, -P - 1, -P + 1, P + 1, P - 1};
-#pragma unroll
-    for (int a = 0; a < 9; a++) {
-        const int so = __builtin_amdgcn_readfirstlane(int((unsigned(a) * plane + unsigned(shift[a])) * 4u));
-        f[a] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, v, so, 0));
-    }
-}
-
-template <bool NT>
-__device__ __forceinline__ void pool_store_buf(__amdgpu_buffer_rsrc_t r, unsigned plane, unsigned i,
-                                               const float f[9])
-{
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        const int so = __builtin_amdgcn_readfirstlane(int(unsigned(k) * plane * 4u));
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f[k]), r, int(i * 4u), so, NT ? 2 : 0);   // 2: nt
-    }
-}
-
-// First phase of a multi-step launch on a 64 x kPool3H tile: step `step` on the tile and a halo
-// of H nodes, from the planes in global memory into the LDS tile, whose slots are laid out with a
-// two-node halo (kPool3EW per row) whatever H is.  Returns whether an own node went bad.  CONV:
-// the convective outlet reads the previous records `prev` and the values this step records at
-// x = nx - 1 go to rec1 for rows y0 - 1 .. y0 + kPool3H (3 x (kPool3H + 2), unwrapped rows).
-template <int S, int H, bool inner, bool CONV = false>
-__device__ __forceinline__ bool pool_first_phase(const PoolSim &d, const typename Codec<S>::elem *src,
-                                                 __amdgpu_buffer_rsrc_t rsrc,
-                                                 typename Codec<S>::elem *mid, int x0, int y0,
-                                                 unsigned step, void *prev = nullptr,
-                                                 typename Codec<S>::real *rec1 = nullptr)
-{
-    using T = typename Codec<S>::real;
-    constexpr int W1 = kPoolTileW + 2 * H, N1 = W1 * (kPool3H + 2 * H);
-    constexpr int odirs[3] = {3, 6, 7};           // the directions entering from x = nx
-    const Geom &g = d.g;
-    const Outlet none{nullptr, nullptr, 0.0};
-    const Outlet out1{prev, nullptr, d.ou};
-    bool bad = false;
-    for (int e = threadIdx.x; e < N1; e += kBlock2) {
-        const int ux = x0 + e % W1 - H, uy = y0 + e / W1 - H;
-        int x = ux, y = uy;
-        if (!inner && !pool_locate(g, ux, uy, H, x, y)) continue;
-        T f[9];
-        int id;
-        if constexpr (inner) pool_pull_buf(rsrc, g.plane, g.pitch, unsigned(y * g.pitch + x), f);
-        else pull<S>(src, x, y, g, CONV ? out1 : none, f);
-        if (CONV && x == g.nx - 1 && uy >= y0 - 1 && uy <= y0 + kPool3H)
-            for (int q = 0; q < 3; q++) rec1[q * (kPool3H + 2) + (uy - y0 + 1)] = f[odirs[q]];
-        const auto m = relax_node(f, d.mask, d.bodies, g, d.p, x, y, id);
-        store_node<S>(mid, kPool3EN, unsigned((uy - y0 + 2) * kPool3EW + (ux - x0 + 2)), f,
-                      unsigned(y * g.pitch + x), step);
-        const bool own = (ux >= x0) & (ux < x0 + kPoolTileW) & (uy >= y0) & (uy < y0 + kPool3H) &
-                         (ux < g.nx) & (uy < g.ny);
-        const double r1 = 1.0 + double(m.drho);
-        bad |= own && !(r1 > 0.0 && r1 < 1e30);
-    }
-    return bad;
-}
-
-// One 64 x kPool3H tile of a binary32 simulation for k (1 to 3) steps from `done`, as the
-// single-simulation kernels compute them: for k = 3 step done on the tile and a two-node halo into
-// LDS, step done + 1 on the tile and a one-node halo in place (its results held in registers
-// until every pull is made), step done + 2 of the tile to global memory; for k = 2 the first
-// phase with a one-node halo and the last; for k = 1 the last alone, from global memory.  On the
-// simulation's final step the tile's FP64 sums go to its slot of the partials (per-wave rows
-// added in order, rows in order).  inner: the tile lies three or more nodes from every edge of a
-// simulation whose planes span less than 4 GB (pool3_inner); then every phase pulls by plain
-// shifts, the first through a buffer resource, and the last stores through one, as the
-// single-simulation three-step kernel does for its inner tiles.  CONV (edge tiles only): the
-// convective outlet, its recorded values passed from phase to phase in LDS (outl_lds) as in the
-// single-simulation three-step kernel, the last phase writing them for the next launch.
-template <int S, bool inner, bool CONV>
-__device__ __forceinline__ void pool_tile3(const PoolSim &d, int tile, long long done, int k,
-                                           unsigned char *lds, double (*part)[kRingWidth],
-                                           double *outl_lds, unsigned *status)
-{
-    using C = Codec<S>;
-    using T = typename C::real;
-    using E = typename C::elem;
-    constexpr int TW = kPoolTileW, TH = kPool3H, EW = kPool3EW, EN = kPool3EN;
-    constexpr bool DPP = wave_sum_dpp<T>();
-    const Geom &g = d.g;
-    const int b = pool_buf(done, d.spl, d.spk);
-    // selects rather than indexing: the kernel holds d in registers, not in memory
-    const E *__restrict__ src = static_cast<const E *>(b ? d.buf[1] : d.buf[0]);
-    E *__restrict__ dst = static_cast<E *>(b ? d.buf[0] : d.buf[1]);
-    const Outlet none{nullptr, nullptr, 0.0};
-    void *const oprev = b ? d.outlet[1] : d.outlet[0];
-    void *const onext = b ? d.outlet[0] : d.outlet[1];
-    constexpr int odirs[3] = {3, 6, 7};           // the directions entering from x = nx
-    T *rec1 = reinterpret_cast<T *>(outl_lds);     // first phase's records, rows y0 - 1 .. y0 + TH
-    T *rec2 = rec1 + 3 * (TH + 2);                 // middle phase's records, rows y0 .. y0 + TH - 1
-    const int x0 = (tile % d.ntx) * TW, y0 = (tile / d.ntx) * TH;
-    E *mid = reinterpret_cast<E *>(lds);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool final_step = done + k == d.target;             // uniform over the workgroup
-    if (final_step && lane < kRingWidth) part[wave][lane] = 0.0;
-    const unsigned long long pbytes = 9ull * (unsigned long long)g.plane * sizeof(E);
-    const __amdgpu_buffer_rsrc_t rsrc = buffer_over(const_cast<E *>(src), unsigned(pbytes));
-    const __amdgpu_buffer_rsrc_t rdst = buffer_over(dst, unsigned(pbytes));
-    bool bad = false;
-    if (k == 3) {
-        bad |= pool_first_phase<S, 2, inner, CONV>(d, src, rsrc, mid, x0, y0, (unsigned)done, oprev, rec1);
-        __syncthreads();
-        constexpr int MW = TW + 2, MN = MW * (TH + 2), R2 = (MN + kBlock2 - 1) / kBlock2;
-        T res[R2][9];
-        int slot[R2];
-        unsigned node[R2];
-#pragma unroll
-        for (int it = 0; it < R2; it++) {
-            const int j = threadIdx.x + it * kBlock2;
-            const int ux = x0 + j % MW - 1, uy = y0 + j / MW - 1;
-            int x = ux, y = uy;
-            slot[it] = -1;
-            node[it] = 0;
-            if (j < MN && (inner || pool_locate(g, ux, uy, 1, x, y))) {
-                int id;
-                if constexpr (inner) pull_tile_shifts<S, 2>(mid, EN, EW, ux, uy, x0, y0, res[it]);
-                else pull_tile<S, 2>(mid, EN, EW, ux, uy, x0, y0, g, res[it]);
-                if (CONV && x == g.nx - 1) {
-                    // the outlet rule of pull, with the first phase's records and neighbours
-                    const T u = T(d.ou);
-                    for (int q = 0; q < 3; q++) {
-                        int pa;
-                        const unsigned jn = tile_source<2>(odirs[q], g.nx - 2, uy, x0, y0, EW, g, pa);
-                        const T nb = C::load(mid + pa * EN, jn, weight<T>(odirs[q]));
-                        res[it][odirs[q]] = (rec1[q * (TH + 2) + (uy - y0 + 1)] + u * nb) / (T(1) + u);
-                    }
-                    if (uy >= y0 && uy < y0 + TH)
-                        for (int q = 0; q < 3; q++) rec2[q * TH + (uy - y0)] = res[it][odirs[q]];
-                }
-                const auto m = relax_node(res[it], d.mask, d.bodies, g, d.p, x, y, id);
-                slot[it] = (j / MW + 1) * EW + j % MW + 1;
-                node[it] = unsigned(y * g.pitch + x);
-                const bool own = (ux >= x0) & (ux < x0 + TW) & (uy >= y0) & (uy < y0 + TH) &
-                                 (ux < g.nx) & (uy < g.ny);
-                const double r1 = 1.0 + double(m.drho);
-                bad |= own && !(r1 > 0.0 && r1 < 1e30);
-            }
-        }
-        __syncthreads();                          // every middle-phase pull has read step done
-#pragma unroll
-        for (int it = 0; it < R2; it++)
-            if (slot[it] >= 0) store_node<S>(mid, EN, unsigned(slot[it]), res[it], node[it], (unsigned)(done + 1));
-        __syncthreads();
-    } else if (k == 2) {
-        bad |= pool_first_phase<S, 1, inner, CONV>(d, src, rsrc, mid, x0, y0, (unsigned)done, oprev, rec1);
-        __syncthreads();
-    }
-    constexpr int R3 = (TW * TH + kBlock2 - 1) / kBlock2;
-#pragma unroll
-    for (int it = 0; it < R3; it++) {
-        const int j = threadIdx.x + it * kBlock2;
-        const int x = x0 + j % TW, y = y0 + j / TW;
-        double rho = 0.0, fx = 0.0, fy = 0.0;
-        int id = 0;
-        if ((j < TW * TH) & (x < g.nx) & (y < g.ny)) {
-            Macro<T> m;
-            if (k == 1) {
-                const Outlet one{oprev, onext, d.ou};
-                m = update_node<S>(src, dst, d.mask, d.bodies, g, CONV ? one : none, d.p, x, y, id,
-                                   (unsigned)done);
-            } else {
-                T f[9];
-                if constexpr (inner) pull_tile_shifts<S, 2>(mid, EN, EW, x, y, x0, y0, f);
-                else pull_tile<S, 2>(mid, EN, EW, x, y, x0, y0, g, f);
-                if (CONV && x == g.nx - 1) {
-                    // the outlet rule with the previous phase's records; this step's go to memory
-                    const T u = T(d.ou);
-                    T *next = static_cast<T *>(onext);
-                    for (int q = 0; q < 3; q++) {
-                        int pa;
-                        const unsigned jn = tile_source<2>(odirs[q], g.nx - 2, y, x0, y0, EW, g, pa);
-                        const T nb = C::load(mid + pa * EN, jn, weight<T>(odirs[q]));
-                        const T pr = k == 3 ? rec2[q * TH + (y - y0)] : rec1[q * (TH + 2) + (y - y0 + 1)];
-                        f[odirs[q]] = (pr + u * nb) / (T(1) + u);
-                    }
-                    for (int q = 0; q < 3; q++) next[q * g.ny + y] = f[odirs[q]];
-                }
-                m = relax_node(f, d.mask, d.bodies, g, d.p, x, y, id);
-                const unsigned i = y * g.pitch + x;
-                if constexpr (!inner) store_node<S>(dst, g.plane, i, f, i, (unsigned)(done + k - 1));
-                else if (d.nt) pool_store_buf<true>(rdst, g.plane, i, f);
-                else pool_store_buf<false>(rdst, g.plane, i, f);
-            }
-            rho = 1.0 + double(m.drho);
-            fx = double(m.fx);
-            fy = double(m.fy);
-            bad |= !(rho > 0.0 && rho < 1e30);
-        }
-        if (final_step) {
-            // this round's nodes into the wave's row (lane 0 of the wave adds, in round order)
-            const double mw = wave_sum<DPP>(rho);
-            if (lane == 0) part[wave][0] += mw;
-            unsigned long long solid = __ballot(id != 0);
-            while (solid) {
-                const int lead = __ffsll((unsigned long long)solid) - 1;
-                const int bb = __shfl(id, lead, 64);
-                const bool mine = id == bb;
-                const double sx = wave_sum<DPP>(mine ? -fx : 0.0);
-                const double sy = wave_sum<DPP>(mine ? -fy : 0.0);
-                if (lane == 0) {
-                    part[wave][1 + 2 * (bb - 1)] += sx;
-                    part[wave][2 + 2 * (bb - 1)] += sy;
-                }
-                solid &= ~__ballot(mine);
-            }
-        }
-    }
-    if (__ballot(bad) && lane == 0) atomicOr(status, 1u);
-    if (final_step) {
-        __syncthreads();
-        if (threadIdx.x < kRingWidth) {
-            double v = 0.0;
-            for (int w = 0; w < kBlock2 / 64; w++) v += part[w][threadIdx.x];
-            d.partials[(size_t)tile * kRingWidth + threadIdx.x] = v;
-        }
-    }
-}
-
-// Whether binary32 tile `tile` of d takes pool_tile3's inner form.
-__device__ __forceinline__ bool pool3_inner(const PoolSim &d, int tile)
-{
-    const Geom &g = d.g;
-    const int x0 = (tile % d.ntx) * kPoolTileW, y0 = (tile / d.ntx) * kPool3H;
-    return (x0 >= 3) & (x0 + kPoolTileW + 3 <= g.nx) & (y0 >= 3) & (y0 + kPool3H + 3 <= g.ny) &
-           (9ull * (unsigned long long)g.plane * 4ull <= 0xFFFFFFFFull);
-}
-
-// Storage formats by kernel: class 1 computes in FP64 (F64, F32D), class 0 in FP32 with 2-byte
-// storage, both two steps per launch; class 2 is binary32 storage, three steps per launch.  Each
-// class has a kernel of its own, so the FP32 formats are not held to the FP64 path's registers
-// and LDS: measured 4 waves per SIMD with one kernel for all.
-__host__ __device__ inline int pool_class(int storage, int conv)
-{
-    return storage == kF64 || storage == kF32D ? 1 : (storage == kF32 ? 2 : 0);
-}
-
-// Tile height and steps per kernel launch of a storage format's class.
-__host__ __device__ inline int pool_tile_h(int storage, int conv) { return pool_class(storage, conv) == 2 ? kPool3H : kPoolTileH; }
-__host__ __device__ inline int pool_spk(int storage, int conv) { return pool_class(storage, conv) == 2 ? 3 : 2; }
-
 // pool_tile with or without the convective outlet (a separate instantiation, as in the
 // single-simulation two-step kernel).
 template <int S>
-__device__ __forceinline__ void pool_tile2(const PoolSim &d, int tile, long long done, int nsteps,
+__device__ __forceinline__ void pool_tile2(const PoolSim &d, int tile, long long done, int nsteps, int b,
                                            unsigned char *lds, double (*part)[kRingWidth], double *outl,
                                            unsigned *status)
 {
-    if (d.conv) pool_tile<S, true>(d, tile, done, nsteps, lds, part, outl, status);
-    else pool_tile<S, false>(d, tile, done, nsteps, lds, part, outl, status);
+    if (d.conv) pool_tile<S, true>(d, tile, done, nsteps, b, lds, part, outl, status);
+    else pool_tile<S, false>(d, tile, done, nsteps, b, lds, part, outl, status);
 }
 
-// Steps t_off .. t_off + nsteps - 1 of the graph replay (nsteps up to the class's steps per
-// launch), for every resident simulation of class CLASS: workgroup w (< *ntiles) updates tile
-// entry w (tiles of the other classes return at once); a simulation with fewer steps left takes
-// those.  The host writes the table in XCD order (upload_tables), so the entry is found without
-// first reading the tile count: the two loads are issued together, and a workgroup starts with
-// two dependent loads (its entry, then its simulation's descriptor) before its populations.
-template <int CLASS>
-__global__ __launch_bounds__(kBlock2) void pool_step_kernel(PoolSim *sims, const TileRef *tiles,
-                                                            const int *ntiles,
-                                                            const long long *t_base, int t_off,
-                                                            int nsteps)
+// One or two steps of every resident simulation that KERNEL (kPoolTiles32: FP32 arithmetic, kPoolTiles64:
+// FP64) takes.  Two kernels, so the FP32 formats are
+// not held to the FP64 path's registers and LDS: measured 4 waves per SIMD with one for all.  The host
+// writes the table in XCD order (upload_tables), so the entry is found without first reading the
+// tile count: the two loads are issued together, and a workgroup starts with two dependent loads
+// (its entry, then its simulation's descriptor) before its populations.
+template <int KERNEL> __global__ __launch_bounds__(kBlock2) void pool_step_kernel(PoolLaunch a)
 {
-    // the LDS tile in the class's widest storage format
-    __shared__ __align__(16) unsigned char lds[CLASS == 2 ? 9 * kPool3EN * 4 : 9 * kPoolEN * (CLASS ? 8 : 4)];
+    // the LDS tile in the kernel's widest storage format
+    __shared__ __align__(16) unsigned char lds[9 * kPoolEN * (KERNEL == kPoolTiles64 ? 8 : 4)];
     __shared__ double part[kBlock2 / 64][kRingWidth];
-    // convective outlet records: pool_tile's 3 x kPoolTileH values of T, pool_tile3's
-    // 3 x (2 kPool3H + 2) binary32 values
-    constexpr int kOutl = CLASS == 2 ? (3 * (2 * kPool3H + 2) + 1) / 2 : 3 * kPoolTileH;
-    __shared__ double outl[kOutl];
-    const int n = *ntiles;
-    const TileRef tr = tiles[blockIdx.x];                     // the table spans the grid
+    __shared__ double outl[3 * kPoolTileH];                   // convective outlet records
+    const int n = *a.ntiles;
+    const TileRef tr = a.tiles[blockIdx.x];                   // the table spans the grid
     if ((int)blockIdx.x >= n) return;                         // uniform over the workgroup
     // A local copy of the descriptor: its fields are read once into scalar registers (read through
     // the pointer, they were read again after stores that might alias it: measured 16% of the
     // kernel's time).  The status flag is written through the pointer.
-    const PoolSim d = sims[tr.slot];
-    unsigned *status = &sims[tr.slot].status;
-    const long long done = *t_base + t_off - d.t0;
-    if (!d.active || done < 0 || done >= d.target) return;    // uniform over the workgroup
-    if (pool_class(d.storage, d.conv) != CLASS) return;
-    const int k = d.target - done < nsteps ? int(d.target - done) : nsteps;
-    if constexpr (CLASS == 2) {
-        if (pool3_inner(d, tr.tile)) pool_tile3<kF32, true, false>(d, tr.tile, done, k, lds, part, outl, status);
-        else if (d.conv) pool_tile3<kF32, false, true>(d, tr.tile, done, k, lds, part, outl, status);
-        else pool_tile3<kF32, false, false>(d, tr.tile, done, k, lds, part, outl, status);
-    } else if constexpr (CLASS == 1) {
-        if (d.storage == kF64) pool_tile2<kF64>(d, tr.tile, done, k, lds, part, outl, status);
-        else pool_tile2<kF32D>(d, tr.tile, done, k, lds, part, outl, status);
+    const PoolSim d = a.sims[tr.slot];
+    unsigned *status = &a.sims[tr.slot].status;
+    const long long start = *a.t_base - d.t0, left = d.target - start;
+    if (!d.active || start < 0 || left <= 0) return;          // uniform over the workgroup
+    const int body = pool_body(d, left), k = body - a.t_off < 2 ? body - a.t_off : 2;
+    if (k <= 0) return;
+    const long long done = start + a.t_off;
+    const int b = (pool_buf(d, start) + a.t_off / 2) & 1;
+    if constexpr (KERNEL == kPoolTiles64) {
+        if (d.storage == kF64) pool_tile2<kF64>(d, tr.tile, done, k, b, lds, part, outl, status);
+        else pool_tile2<kF32D>(d, tr.tile, done, k, b, lds, part, outl, status);
     } else {
         switch (d.storage) {
-        case kF16S: pool_tile2<kF16S>(d, tr.tile, done, k, lds, part, outl, status); break;
-        case kF16SR: pool_tile2<kF16SR>(d, tr.tile, done, k, lds, part, outl, status); break;
-        case kBF16SR: pool_tile2<kBF16SR>(d, tr.tile, done, k, lds, part, outl, status); break;
-        default: pool_tile2<kBF16S>(d, tr.tile, done, k, lds, part, outl, status); break;
+        case kF32: pool_tile2<kF32>(d, tr.tile, done, k, b, lds, part, outl, status); break;
+        case kF16S: pool_tile2<kF16S>(d, tr.tile, done, k, b, lds, part, outl, status); break;
+        case kF16SR: pool_tile2<kF16SR>(d, tr.tile, done, k, b, lds, part, outl, status); break;
+        case kBF16SR: pool_tile2<kBF16SR>(d, tr.tile, done, k, b, lds, part, outl, status); break;
+        default: pool_tile2<kBF16S>(d, tr.tile, done, k, b, lds, part, outl, status); break;
         }
     }
 }
@@ -598,7 +273,7 @@ __device__ __forceinline__ void pool_residual_node(const PoolSim &d, int parity,
     d.snap[n + i] = uy;
 }
 
-// One workgroup per tile, as the step kernel; per-tile sums (waves in a fixed order).
+// One workgroup per table entry; sums per tile or block (waves in a fixed order).
 __global__ __launch_bounds__(kBlock2) void pool_residual_kernel(PoolSim *sims, const TileRef *tiles,
                                                                 const int *ntiles,
                                                                 const long long *t_base, int t_off)
@@ -611,37 +286,40 @@ __global__ __launch_bounds__(kBlock2) void pool_residual_kernel(PoolSim *sims, c
     const PoolSim &d = sims[tr.slot];
     const long long done = *t_base + t_off - d.t0;
     if (!residual_due(d, done)) return;                       // uniform over the workgroup
-    const int x = (tr.tile % d.ntx) * kPoolTileW + lane;
-    const int y0 = (tr.tile / d.ntx) * d.th;
-    double d2 = 0.0, u2 = 0.0;
-    const int parity = pool_buf(done, d.spl, d.spk);
-    for (int r = wave; r < d.th; r += kBlock2 / 64) {          // rows of the tile, in order
-        const int y = y0 + r;
-        if (x >= d.g.nx || y >= d.g.ny) continue;
-        double a2 = 0.0, b2 = 0.0;
-        switch (d.storage) {
-        case kF64: pool_residual_node<kF64>(d, parity, x, y, a2, b2); break;
-        case kF32: pool_residual_node<kF32>(d, parity, x, y, a2, b2); break;
-        case kF16S: pool_residual_node<kF16S>(d, parity, x, y, a2, b2); break;
-        case kF32D: pool_residual_node<kF32D>(d, parity, x, y, a2, b2); break;
-        case kF16SR: pool_residual_node<kF16SR>(d, parity, x, y, a2, b2); break;
-        case kBF16SR: pool_residual_node<kBF16SR>(d, parity, x, y, a2, b2); break;
-        default: pool_residual_node<kBF16S>(d, parity, x, y, a2, b2); break;
+    const int x = tr.x0 + lane, width = tr.w;
+    const int parity = pool_buf(d, done);
+    const int rows = tr.kernel >= kPoolStrips ? pool_block_rows(tr.form) : tr.y1 - tr.y0;
+    for (int y0 = tr.y0, block = tr.tile; y0 < tr.y1; y0 += rows, block++) {   // a strip's blocks
+        const int y1 = y0 + rows < tr.y1 ? y0 + rows : tr.y1;
+        double d2 = 0.0, u2 = 0.0;
+        for (int y = y0 + wave; y < y1; y += kBlock2 / 64) {   // rows, in order
+            if (lane >= width || x >= d.g.nx) continue;
+            double a2 = 0.0, b2 = 0.0;
+            switch (d.storage) {
+            case kF64: pool_residual_node<kF64>(d, parity, x, y, a2, b2); break;
+            case kF32: pool_residual_node<kF32>(d, parity, x, y, a2, b2); break;
+            case kF16S: pool_residual_node<kF16S>(d, parity, x, y, a2, b2); break;
+            case kF32D: pool_residual_node<kF32D>(d, parity, x, y, a2, b2); break;
+            case kF16SR: pool_residual_node<kF16SR>(d, parity, x, y, a2, b2); break;
+            case kBF16SR: pool_residual_node<kBF16SR>(d, parity, x, y, a2, b2); break;
+            default: pool_residual_node<kBF16S>(d, parity, x, y, a2, b2); break;
+            }
+            d2 += a2;
+            u2 += b2;
         }
-        d2 += a2;
-        u2 += b2;
-    }
-    d2 = wave_sum(d2);
-    u2 = wave_sum(u2);
-    if (lane == 0) {
-        part[wave][0] = d2;
-        part[wave][1] = u2;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        double v = 0.0;
-        for (int w = 0; w < kBlock2 / 64; w++) v += part[w][threadIdx.x];
-        d.rpart[2 * tr.tile + threadIdx.x] = v;
+        d2 = wave_sum(d2);
+        u2 = wave_sum(u2);
+        __syncthreads();                                      // the block before is written
+        if (lane == 0) {
+            part[wave][0] = d2;
+            part[wave][1] = u2;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double v = 0.0;
+            for (int w = 0; w < kBlock2 / 64; w++) v += part[w][threadIdx.x];
+            d.rpart[2 * block + threadIdx.x] = v;
+        }
     }
 }
 
@@ -703,8 +381,9 @@ struct Request {
     void *outlet[2] = {nullptr, nullptr};
 };
 
-int pool_geometry(const vplbm_config &c, Geom &g, int &ntx, int &ntiles)
+Geom pool_geometry(const vplbm_config &c)
 {
+    Geom g{};
     g.nx = c.nx;
     g.ny = c.ny;
     g.pitch = (c.nx + 63) / 64 * 64;
@@ -712,17 +391,57 @@ int pool_geometry(const vplbm_config &c, Geom &g, int &ntx, int &ntiles)
     g.xper = c.bc_xlo == VPLBM_PERIODIC;
     g.yper = c.bc_ylo == VPLBM_PERIODIC;
     g.inlet = c.bc_xlo == VPLBM_VELOCITY;
-    const int th = pool_tile_h(c.storage, c.bc_xhi == VPLBM_CONVECTIVE);
-    ntx = (c.nx + kPoolTileW - 1) / kPoolTileW;
-    ntiles = ntx * ((c.ny + th - 1) / th);
-    return VPLBM_OK;
+    return g;
 }
+
+// The kernel for a simulation.  The strip sweep needs the planes within its 32-bit offsets and a row of
+// the lattice for every step.
+int pool_kernel(int storage, const Geom &g)
+{
+    const PoolStrips *strips = pool_strips(storage);
+    if (strips && 9ull * (unsigned long long)g.plane * elem_bytes(storage) <= 0xFFFFFFFFull && g.ny >= strips->steps) return kPoolStrips + storage;
+    return storage == kF64 || storage == kF32D ? kPoolTiles64 : kPoolTiles32;
+}
+
+const PoolStrips &strips_of(int kernel) { return *pool_strips(pool_storage(kernel)); }
+
+// Kernel `kernel` for the main launches of d, `done` steps done, at a replay boundary.
+void set_kernel(PoolSim &d, int kernel, long long done)
+{
+    const int buf = d.spk ? pool_buf(d, done) : 0;
+    const bool strips = kernel >= kPoolStrips && kernel < kPoolPatches;
+    d.kernel = kernel;
+    d.from = done;
+    d.from_buf = buf;
+    d.spk = kernel < kPoolStrips ? 2 : strips ? strips_of(kernel).steps : pool_patches(kernel).steps;
+    d.body = strips ? d.spl / d.tail * d.tail : d.spl;
+    d.launches = (d.body + d.spk - 1) / d.spk + (d.body < d.spl);
+}
+
+// Tiles that a simulation's memory is counted with: those of 64 x 8 nodes, for binary32 64 x 14.  (A
+// strip's blocks are of 8 rows at most: up to twice as many, a 500th part of the simulation's memory.)
+int count_tiles(const Geom &g, int storage)
+{
+    const int th = storage == kF32 ? 14 : kPoolTileH;
+    return (g.nx + kPoolTileW - 1) / kPoolTileW * ((g.ny + th - 1) / th);
+}
+
+// What the strips of a simulation are made of (StripPlan's segments): nothing but the simulation
+// decides on them.
+std::vector<StripTile> pool_segments(const Request &r, const Geom &g, int kernel)
+{
+    const PoolStrips &shape = strips_of(kernel);
+    int box[kMaxBodies][4], nbox = 0;
+    for (const vplbm_body &b : r.bodies) nbox += body_box(g, b, box[nbox]);
+    return strip_segments({g.nx, g.ny, g.xper != 0, g.yper != 0, shape.own + 2 * shape.halo, shape.halo, shape.steps, nbox, box});
+}
+
+int segment_blocks(const StripTile &s) { return (s.y1 - s.y0 + pool_block_rows(s.form) - 1) / pool_block_rows(s.form); }
 
 uint64_t bytes_needed(const vplbm_config &c, bool stop = false)
 {
-    Geom g;
-    int ntx, ntiles;
-    pool_geometry(c, g, ntx, ntiles);
+    const Geom g = pool_geometry(c);
+    const int ntiles = count_tiles(g, c.storage);
     const uint64_t pop = (uint64_t)9 * g.plane * elem_bytes(c.storage);
     const uint64_t residual = stop ? 2 * (uint64_t)g.nx * g.ny * sizeof(double) + (uint64_t)ntiles * 2 * sizeof(double) : 0;
     const uint64_t outlet = c.bc_xhi == VPLBM_CONVECTIVE ? 2 * 3 * (uint64_t)g.ny * sizeof(double) : 0;
@@ -749,22 +468,24 @@ struct vplbm_pool_s {
     bool own_stream = false;
     hipStream_t cap_stream = nullptr;
     hipGraphExec_t graph = nullptr;
-    int grid_cap = 0;                     // workgroups per launch in the captured graph
     bool graph_checks = false;            // the graph ends with the residual-check kernels
-    int graph_classes = 0;                // storage classes the graph has step kernels for
+    int graph_kernels = 0;                // step kernels in the graph (bits)
     PoolSim *d_sims = nullptr;
-    TileRef *d_tiles = nullptr;
-    int *d_ntiles = nullptr;
+    TileRef *d_tiles = nullptr;           // the kernels' tables, one after the other
+    int *d_ntiles = nullptr;              // entries of each
     long long *d_t = nullptr;             // pool step counter (steps every resident sim has run)
     long long *d_zero = nullptr;
     double *staging = nullptr;
     size_t staging_bytes = 0;
     HostCopy host_copy;                   // results to host memory
     int tile_cap = 0;
-    int ntiles = 0;
+    // Of each kernel's table: where it begins, its workgroups per launch in the captured graph (as many
+    // entries are there), and the entries that count.
+    int table_at[kPoolKernels] = {}, table_cap[kPoolKernels] = {}, table_n[kPoolKernels] = {};
     long long t_host = 0;                 // host copy of *d_t after the last finished chunk
     std::vector<PoolSim> h_sims;
     std::vector<int64_t> slot_req;        // request id per slot (-1 free)
+    std::vector<std::vector<StripTile>> segments;   // per slot: what its strips are made of
     std::map<int64_t, Request> reqs;
     std::deque<int64_t> queue;
     std::deque<Leaving> leaving;          // retired, in the order they are released
@@ -875,7 +596,7 @@ int release(vplbm_pool p, hipStream_t st)
             r.fields.reset(new (std::nothrow) double[3 * n]);
             if (!r.fields) return fail(VPLBM_ENOMEM, "cannot allocate the host arrays of a result");
             StepArgs a{};
-            const int pb = pool_buf(r.done, d.spl, d.spk);
+            const int pb = pool_buf_after(d, r.done);
             a.src = d.buf[pb];                          // the state after the steps done
             a.outlet.prev = d.conv ? d.outlet[pb] : nullptr;
             a.outlet.u = d.ou;
@@ -905,7 +626,19 @@ int admit(vplbm_pool p, Request &r, int slot)
     const AdmissionState st{p->used, p->cfg.budget_bytes, p->resident_nodes, p->max_nodes, 1};
     if (!may_admit(st, r.bytes, nodes)) return 0;
     PoolSim d{};
-    pool_geometry(r.cfg, d.g, d.ntx, d.ntiles);
+    d.g = pool_geometry(r.cfg);
+    const int kernel = pool_kernel(r.cfg.storage, d.g);
+    d.spl = p->cfg.steps_per_launch;
+    d.tail = kernel >= kPoolStrips ? strips_of(kernel).steps : 0;
+    set_kernel(d, kernel, 0);
+    std::vector<StripTile> segments;
+    d.ntx = (d.g.nx + kPoolTileW - 1) / kPoolTileW;
+    d.ntiles = d.ntx * ((d.g.ny + kPoolTileH - 1) / kPoolTileH);
+    if (d.tail) {
+        segments = pool_segments(r, d.g, kernel);
+        d.ntiles = 0;
+        for (const StripTile &s : segments) d.ntiles += segment_blocks(s);
+    }
     const int conv = r.cfg.bc_xhi == VPLBM_CONVECTIVE ? 1 : 0;
     const size_t pop = (size_t)9 * d.g.plane * elem_bytes(r.cfg.storage);
     struct { void **ptr; size_t n; } allocs[] = {
@@ -948,10 +681,7 @@ int admit(vplbm_pool p, Request &r, int slot)
     d.ou = r.cfg.u_in_x;
     d.outlet[0] = r.outlet[0];
     d.outlet[1] = r.outlet[1];
-    d.th = pool_tile_h(d.storage, conv);
-    d.spk = pool_spk(d.storage, conv);
     d.active = 1;
-    d.spl = p->cfg.steps_per_launch;
     d.t0 = p->t_host;
     d.target = r.nsteps;
     d.tol = r.tol;
@@ -974,6 +704,7 @@ int admit(vplbm_pool p, Request &r, int slot)
     // the body table copy above reads `hp` from the stack: let it land before returning
     HIP_TRY(hipStreamSynchronize(p->stream));
     p->h_sims[slot] = d;
+    p->segments[slot] = std::move(segments);
     r.slot = slot;
     r.state = VPLBM_RUNNING;
     p->used += r.bytes;
@@ -987,53 +718,54 @@ int admit(vplbm_pool p, Request &r, int slot)
 int ensure_pool_graph(vplbm_pool p)
 {
     bool checks = false;
-    int classes = 0;                      // bit c: a simulation of class c is resident
+    int kernels = 0;                      // bit k: a simulation of kernel k is resident
     for (const PoolSim &d : p->h_sims) {
         checks |= d.active && d.tol > 0.0;
-        if (d.active) classes |= 1 << pool_class(d.storage, d.conv);
+        if (d.active) kernels |= 1 << d.kernel;
     }
-    if (!classes) classes = 1;
-    if (p->graph && p->grid_cap >= p->ntiles && p->grid_cap <= 8 * (p->ntiles > 4096 ? p->ntiles : 4096) &&
-        p->graph_checks == checks && p->graph_classes == classes)
-        return VPLBM_OK;
+    if (p->graph && p->graph_checks == checks && p->graph_kernels == kernels) return VPLBM_OK;
     if (p->graph) {
         HIP_TRY(hipGraphExecDestroy(p->graph));
         p->graph = nullptr;
     }
-    int cap = 4096;
-    while (cap < p->ntiles) cap *= 2;
-    // every workgroup reads its table entry before it compares its index with the tile count
-    if (cap > p->tile_cap) return fail(VPLBM_EHIP, "tile table (%d entries) shorter than the grid (%d)", p->tile_cap, cap);
-    p->grid_cap = cap;
+    int cap = 0;
+    for (int kernel = 0; kernel < kPoolKernels; kernel++) cap += p->table_cap[kernel];
     host_log("pool %p: capture the step graph (%d workgroups per launch, %d steps, residual checks %d)",
         (void *)p, cap, p->cfg.steps_per_launch, (int)checks);
     if (!p->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
     hipGraph_t graph = nullptr;
     HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
-    // Each class's launches from the replay's start: spk steps each (2, or 3 for binary32), what
-    // remains last (pool_buf counts launches this way).  The classes advance the same steps.
+    // Each kernel's launches from the replay's start: its steps each (PoolSim::spk), what remains
+    // last (pool_buf counts launches this way).  The kernels advance the same steps.
     const int spl = p->cfg.steps_per_launch;
-    for (int j = 0; j < spl && e == hipSuccess; j += 2) {
-        const int nsteps = spl - j >= 2 ? 2 : 1;
-        if (classes & 1) {
-            pool_step_kernel<0><<<dim3(cap), dim3(kBlock2), 0, p->cap_stream>>>(p->d_sims, p->d_tiles, p->d_ntiles, p->d_t, j, nsteps);
-            e = hipGetLastError();
+    auto launch_on = [&](int table) { return PoolLaunch{p->d_sims, p->d_tiles + p->table_at[table], p->d_ntiles + table, p->d_t, 0}; };
+    for (int kernel = 0; kernel < kPoolKernels; kernel++) {
+        if (!(kernels >> kernel & 1)) continue;
+        const int cap = p->table_cap[kernel];
+        PoolLaunch a = launch_on(kernel);
+        if (kernel >= kPoolStrips) {
+            const auto launch = kernel < kPoolPatches ? strips_of(kernel).launch : pool_patches(kernel).launch;
+            if (e == hipSuccess) e = launch(a, spl, cap, p->cap_stream);
+            continue;
         }
-        if (e == hipSuccess && (classes & 2)) {
-            pool_step_kernel<1><<<dim3(cap), dim3(kBlock2), 0, p->cap_stream>>>(p->d_sims, p->d_tiles, p->d_ntiles, p->d_t, j, nsteps);
+        for (int j = 0; j < spl && e == hipSuccess; j += 2) {
+            a.t_off = j;
+            if (kernel == kPoolTiles32) pool_step_kernel<kPoolTiles32><<<dim3(cap), dim3(kBlock2), 0, p->cap_stream>>>(a);
+            else pool_step_kernel<kPoolTiles64><<<dim3(cap), dim3(kBlock2), 0, p->cap_stream>>>(a);
             e = hipGetLastError();
         }
     }
-    for (int j = 0; j < spl && e == hipSuccess && (classes & 4); j += 3) {
-        const int nsteps = spl - j >= 3 ? 3 : spl - j;
-        pool_step_kernel<2><<<dim3(cap), dim3(kBlock2), 0, p->cap_stream>>>(p->d_sims, p->d_tiles, p->d_ntiles, p->d_t, j, nsteps);
-        e = hipGetLastError();
-    }
+    for (int table = kPoolStrips; table < kPoolPatches; table++)   // every format's strips: the tails
+        if (e == hipSuccess && p->table_cap[table]) e = strips_of(table).tail(launch_on(table), p->table_cap[table], p->cap_stream);
     if (e == hipSuccess && checks) {
         const int n = p->cfg.steps_per_launch;
-        pool_residual_kernel<<<dim3(cap), dim3(kBlock2), 0, p->cap_stream>>>(p->d_sims, p->d_tiles, p->d_ntiles, p->d_t, n);
-        e = hipGetLastError();
+        for (int table = 0; table < kPoolPatches && e == hipSuccess; table++) {
+            if (!p->table_cap[table]) continue;
+            const PoolLaunch a = launch_on(table);
+            pool_residual_kernel<<<dim3(p->table_cap[table]), dim3(kBlock2), 0, p->cap_stream>>>(a.sims, a.tiles, a.ntiles, a.t_base, n);
+            e = hipGetLastError();
+        }
         if (e == hipSuccess) {
             pool_residual_fold_kernel<<<dim3(p->cfg.max_slots), dim3(64), 0, p->cap_stream>>>(p->d_sims, p->d_t, n);
             e = hipGetLastError();
@@ -1044,7 +776,7 @@ int ensure_pool_graph(vplbm_pool p)
         e = hipGetLastError();
     }
     p->graph_checks = checks;
-    p->graph_classes = classes;
+    p->graph_kernels = kernels;
     hipError_t e2 = hipStreamEndCapture(p->cap_stream, &graph);
     if (e != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -1057,43 +789,118 @@ int ensure_pool_graph(vplbm_pool p)
     return VPLBM_OK;
 }
 
+// The strips of every resident simulation of a format, sorted by rows and columns (patches leave the
+// tail of a replay to them): blocks of a segment
+// together until all of them make as many strips as the GPU holds waves.  14 simulations of 4.9 million
+// nodes, us per step: 41 with half as many strips, 33.7 with 0.8, 32.7, 34.5 with 1.2, 32.2 with twice as
+// many; the last five of them, 1.6 million: 13.8, 13.1, 12.8, 12.5, 12.4.
+void pool_strip_entries(vplbm_pool p, int storage, std::vector<TileRef> &out)
+{
+    const PoolStrips &shape = *pool_strips(storage);
+    auto takes = [&](const PoolSim &d) { return d.active && d.tail && d.storage == storage; };
+    int most = 0;
+    for (const PoolSim &d : p->h_sims)
+        if (takes(d)) most = std::max(most, d.g.ny);
+    if (!most) return;
+    auto pieces = [&](const StripTile &s, double t) {   // strips of a segment
+        const int m = std::max(1, strip_rows(t, s.form, shape.steps) / pool_block_rows(s.form));
+        return (segment_blocks(s) + m - 1) / m;
+    };
+    const double t = strip_time(shape.steps, most, 1024 * shape.waves * 39 / 40, [&](double t) {
+        long long n = 0;
+        for (int s = 0; s < p->cfg.max_slots; s++)
+            if (takes(p->h_sims[s]))
+                for (const StripTile &g : p->segments[s]) n += pieces(g, t);
+        return n;
+    });
+    for (int s = 0; s < p->cfg.max_slots; s++) {
+        if (!takes(p->h_sims[s])) continue;
+        const size_t first = out.size();
+        int tile = 0;
+        for (const StripTile &g : p->segments[s]) {
+            const int blocks = segment_blocks(g), rows = pool_block_rows(g.form), n = pieces(g, t);
+            for (int i = 0; i < n; i++) {
+                const int b0 = (int)((long long)blocks * i / n), b1 = (int)((long long)blocks * (i + 1) / n);
+                out.push_back({s, tile + b0, kPoolStrips + storage, g.x0, shape.own, g.y0 + b0 * rows, std::min(g.y0 + b1 * rows, g.y1), g.form});
+            }
+            tile += blocks;
+        }
+        std::stable_sort(out.begin() + first, out.end(), [](const TileRef &a, const TileRef &b) {
+            return a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0;
+        });
+    }
+}
+
+// The kernels of the simulations that strips or patches advance, for what is resident now (at a replay
+// boundary): a change goes on from the buffer that holds the state.
+void choose_kernels(vplbm_pool p)
+{
+    for (PoolSim &d : p->h_sims) {
+        if (!d.active || !d.tail) continue;
+        const int kernel = pool_choose(d.storage, (long long)p->resident_nodes);
+        if (kernel != d.kernel) set_kernel(d, kernel, p->t_host - d.t0);
+    }
+}
+
 int upload_tables(vplbm_pool p)
 {
-    std::vector<TileRef> tiles;
-    uint64_t pop_bytes = 0;   // both population buffers of every resident simulation
+    choose_kernels(p);
+    std::vector<TileRef> table[kPoolKernels];
     for (int s = 0; s < p->cfg.max_slots; s++) {
         const PoolSim &d = p->h_sims[s];
-        if (!d.active) continue;
-        for (int t = 0; t < d.ntiles; t++) tiles.push_back({s, t});
-        pop_bytes += (uint64_t)2 * 9 * d.g.plane * elem_bytes(d.storage);
+        if (!d.active || (d.kernel >= kPoolStrips && d.kernel < kPoolPatches)) continue;
+        const bool patches = d.kernel >= kPoolPatches;
+        const int w = patches ? pool_patches(d.kernel).w : kPoolTileW, h = patches ? pool_patches(d.kernel).h : kPoolTileH;
+        int t = 0;
+        for (int y0 = 0; y0 < d.g.ny; y0 += h)
+            for (int x0 = 0; x0 < d.g.nx; x0 += w) table[d.kernel].push_back({s, t++, d.kernel, x0, w, y0, std::min(y0 + h, d.g.ny), 0});
     }
-    // Non-temporal stores once the resident populations exceed what the cache keeps (the rule of
-    // a single simulation, applied to the whole pool: every launch reads them all again).
-    for (int s = 0; s < p->cfg.max_slots; s++)
-        if (p->h_sims[s].active) p->h_sims[s].nt = pop_bytes > ((uint64_t)192 << 20) ? 1 : 0;
-    if ((int)tiles.size() > p->tile_cap) {
-        HIP_TRY(hipStreamSynchronize(p->stream));
-        if (p->d_tiles) HIP_TRY(hipFree(p->d_tiles));
-        p->d_tiles = nullptr;
-        int cap = p->tile_cap ? p->tile_cap : 4096;
-        while (cap < (int)tiles.size()) cap *= 2;
-        if (hipMalloc(&p->d_tiles, sizeof(TileRef) * cap) != hipSuccess) {
-            (void)hipGetLastError();
-            p->tile_cap = 0;
-            return fail(VPLBM_ENOMEM, "cannot allocate the tile table");
+    for (int kernel = kPoolStrips; kernel < kPoolPatches; kernel++)
+        if (pool_strips(pool_storage(kernel))) pool_strip_entries(p, pool_storage(kernel), table[kernel]);
+    // A table that outgrows its part, or fills little of it (workgroups without an entry cost time too:
+    // 4096 of 768 threads 4 us), moves all of them, and the graph is captured again.
+    bool move = false;
+    for (int k = 0; k < kPoolKernels; k++) {
+        const int n = (int)table[k].size(), cap = p->table_cap[k];
+        move |= n > cap || (n == 0) != (cap == 0) || cap > 4 * std::max(n, 64);
+    }
+    if (move) {
+        int total = 0;
+        for (int k = 0; k < kPoolKernels; k++) {
+            const int n = (int)table[k].size();
+            int cap = n ? 64 : 0;
+            while (cap < n) cap *= 2;
+            p->table_at[k] = total;
+            p->table_cap[k] = cap;
+            total += cap;
         }
-        p->tile_cap = cap;
-        if (p->graph) {   // the graph holds the table pointer: capture again
+        HIP_TRY(hipStreamSynchronize(p->stream));
+        if (p->graph) {
             HIP_TRY(hipGraphExecDestroy(p->graph));
             p->graph = nullptr;
         }
+        if (total > p->tile_cap) {
+            if (p->d_tiles) HIP_TRY(hipFree(p->d_tiles));
+            p->d_tiles = nullptr;
+            p->tile_cap = 0;
+            int cap = 4096;
+            while (cap < total) cap *= 2;
+            if (hipMalloc(&p->d_tiles, sizeof(TileRef) * cap) != hipSuccess) {
+                (void)hipGetLastError();
+                memset(p->table_cap, 0, sizeof p->table_cap);
+                return fail(VPLBM_ENOMEM, "cannot allocate the tile table");
+            }
+            p->tile_cap = cap;
+        }
     }
-    const int n = (int)tiles.size();
-    p->ntiles = n;
-    std::vector<TileRef> order(n);
-    for (int b = 0; b < n; b++) order[b] = tiles[xcd_entry(b, n)];
-    if (n) HIP_TRY(hipMemcpyAsync(p->d_tiles, order.data(), sizeof(TileRef) * n, hipMemcpyHostToDevice, p->stream));
-    HIP_TRY(hipMemcpyAsync(p->d_ntiles, &n, sizeof n, hipMemcpyHostToDevice, p->stream));
+    std::vector<TileRef> order;
+    for (int k = 0; k < kPoolKernels; k++) {
+        const int n = p->table_n[k] = (int)table[k].size();
+        for (int b = 0; b < n; b++) order.push_back(table[k][xcd_entry(b, n)]);
+        order.resize(p->table_at[k] + p->table_cap[k], TileRef{});
+    }
+    if (!order.empty()) HIP_TRY(hipMemcpyAsync(p->d_tiles, order.data(), sizeof(TileRef) * order.size(), hipMemcpyHostToDevice, p->stream));
+    HIP_TRY(hipMemcpyAsync(p->d_ntiles, p->table_n, sizeof p->table_n, hipMemcpyHostToDevice, p->stream));
     HIP_TRY(hipMemcpyAsync(p->d_sims, p->h_sims.data(), sizeof(PoolSim) * p->cfg.max_slots, hipMemcpyHostToDevice, p->stream));
     // The host copies above read memory that changes on the next call: finish them.
     HIP_TRY(hipStreamSynchronize(p->stream));
@@ -1136,13 +943,14 @@ int vplbm_pool_create(const vplbm_pool_config *cfg, vplbm_pool *out)
     p->h_sims.assign(cfg->max_slots, PoolSim{});
     memset(p->h_sims.data(), 0, sizeof(PoolSim) * cfg->max_slots);
     p->slot_req.assign(cfg->max_slots, -1);
+    p->segments.resize(cfg->max_slots);
     hipError_t e = hipMalloc(&p->d_sims, sizeof(PoolSim) * cfg->max_slots);
-    if (e == hipSuccess) e = hipMalloc(&p->d_ntiles, sizeof(int));
+    if (e == hipSuccess) e = hipMalloc(&p->d_ntiles, sizeof(int) * kPoolKernels);
     if (e == hipSuccess) e = hipMalloc(&p->d_zero, sizeof(long long));
     if (e == hipSuccess) e = hipMalloc(&p->d_t, sizeof(long long));
     if (e == hipSuccess) e = hipMemsetAsync(p->d_zero, 0, sizeof(long long), p->stream);
     if (e == hipSuccess) e = hipMemsetAsync(p->d_t, 0, sizeof(long long), p->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(p->d_ntiles, 0, sizeof(int), p->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(p->d_ntiles, 0, sizeof(int) * kPoolKernels, p->stream);
     if (e == hipSuccess) e = hipMemsetAsync(p->d_sims, 0, sizeof(PoolSim) * cfg->max_slots, p->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
     if (e != hipSuccess) {

@@ -335,23 +335,6 @@ hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int 
     return launch_advance(s->t_dev, n, st);
 }
 
-// Box of the nodes that body b may cover at any time, clipped to the lattice: 0 if there are none.
-int body_box(const Geom &g, const vplbm_body &b, int box[4])
-{
-    double ex = b.kind == VPLBM_RECT ? b.hx : b.r, ey = b.kind == VPLBM_RECT ? b.hy : b.r;
-    if (b.kind == VPLBM_DISK_OUTSIDE) ex = ey = INFINITY;
-    ex += fabs(b.ax) + 2.0;
-    ey += fabs(b.ay) + 2.0;
-    const double x0 = fmax(floor(b.cx - ex), 0.0), x1 = fmin(ceil(b.cx + ex), g.nx - 1.0);
-    const double y0 = fmax(floor(b.cy - ey), 0.0), y1 = fmin(ceil(b.cy + ey), g.ny - 1.0);
-    if (!(x1 >= x0 && y1 >= y0)) return 0;
-    box[0] = (int)x0;
-    box[1] = (int)y0;
-    box[2] = (int)(x1 - x0) + 1;
-    box[3] = (int)(y1 - y0) + 1;
-    return 1;
-}
-
 // Box of the solid nodes of a host mask: 0 if there are none.
 int mask_box(const Geom &g, const uint8_t *id, int box[4])
 {
@@ -452,6 +435,22 @@ void release(vplbm_sim s)
 }  // namespace
 
 namespace vplbm {
+
+int body_box(const Geom &g, const vplbm_body &b, int box[4])
+{
+    double ex = b.kind == VPLBM_RECT ? b.hx : b.r, ey = b.kind == VPLBM_RECT ? b.hy : b.r;
+    if (b.kind == VPLBM_DISK_OUTSIDE) ex = ey = INFINITY;
+    ex += fabs(b.ax) + 2.0;
+    ey += fabs(b.ay) + 2.0;
+    const double x0 = fmax(floor(b.cx - ex), 0.0), x1 = fmin(ceil(b.cx + ex), g.nx - 1.0);
+    const double y0 = fmax(floor(b.cy - ey), 0.0), y1 = fmin(ceil(b.cy + ey), g.ny - 1.0);
+    if (!(x1 >= x0 && y1 >= y0)) return 0;
+    box[0] = (int)x0;
+    box[1] = (int)y0;
+    box[2] = (int)(x1 - x0) + 1;
+    box[3] = (int)(y1 - y0) + 1;
+    return 1;
+}
 
 NodeParams node_params(const vplbm_config &c)
 {

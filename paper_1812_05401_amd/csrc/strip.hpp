@@ -315,16 +315,17 @@ template <typename T, int K> struct StripShared {
     T record[K][2][3];                // per step: outlet records of the last two rows, by row parity
 };
 
-// K steps of one strip.  mass: per step, this lane's sum of drho over the strip's own nodes.  Returns
-// (job.reduce) whether an own node of this lane had a non-finite or non-positive density.
-template <int S, int C, int K, bool GENERAL>
+// K steps of one strip of windows laid out for KW.  mass: per step, this lane's sum of drho over the
+// strip's own nodes.  Returns (job.reduce) whether an own node of this lane had a non-finite or
+// non-positive density.  SUMS: the forces are added into shared.part (job.reduce).
+template <int S, int C, int K, bool GENERAL, int KW = K, bool SUMS = true>
 __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[K],
-                                            StripShared<typename Codec<S>::real, K> &shared)
+                                            StripShared<typename Codec<S>::real, KW> &shared)
 {
     using P = Cols<S, C>;
     using E = typename Codec<S>::elem;
     using T = typename Codec<S>::real;
-    constexpr int HX = strip_halo<S, C, K>(), ES = (int)sizeof(E);
+    constexpr int HX = strip_halo<S, C, KW>(), ES = (int)sizeof(E);
     constexpr int mirror_y[9] = {0, 1, 4, 3, 2, 8, 7, 6, 5};
     constexpr int cx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
     constexpr int cy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
@@ -472,7 +473,7 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
                 if (id) body_velocity(shared.body[k][id - 1], c ? x1 : x0, yw, usx, usy);
                 drho[c] = relax_solid(h[c], id != 0, usx, usy, rates, fx, fy);
                 keep(c, h[c]);
-                if (job.reduce && row_own && id && (c ? own1 : own0)) {
+                if (SUMS && job.reduce && row_own && id && (c ? own1 : own0)) {
                     double *slot = shared.part[k][lane % kForceSlots] + 2 * id;
                     unsafeAtomicAdd(slot - 1, -double(fx));   // LDS adds that nothing waits for
                     unsafeAtomicAdd(slot, -double(fy));

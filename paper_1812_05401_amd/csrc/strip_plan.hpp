@@ -26,14 +26,10 @@ struct StripPlan {
 // may take the penalized collision; windows at an x edge load column by column.
 inline double strip_row_cost(int form) { return form == kPlain ? 1.0 : form == kMasked ? 2.0 : 1.4; }
 
-// The strips of a lattice, at most `slots` of them if that can be: every strip takes about the same
-// time, so that strips resident together end together.  Sorted by rows, then columns.
-inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
+// The rows of each window that take one form (a StripTile each), to be cut into strips.
+inline std::vector<StripTile> strip_segments(const StripPlan &p)
 {
-    struct Segment {
-        int x0, y0, y1, form;
-    };
-    std::vector<Segment> segs;
+    std::vector<StripTile> segs;
     const int own = p.window - 2 * p.halo, reach = p.steps - 1;
     std::vector<char> solid(p.ny);
     for (int x0 = 0; x0 < p.nx; x0 += own) {
@@ -59,28 +55,44 @@ inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
             y = e;
         }
     }
-    // Rows of a strip of one form within time t: its rows and those it computes beyond them.
-    auto rows = [&](double t, int form) {
-        const int r = (int)(t / strip_row_cost(form)) - 2 * reach;
-        return r < 1 ? 1 : r;
-    };
-    auto count = [&](double t) {
-        long long n = 0;
-        for (const Segment &s : segs) {
-            const int r = rows(t, s.form);
-            n += (s.y1 - s.y0 + r - 1) / r;
-        }
-        return n;
-    };
-    double lo = 2 * reach + 1, hi = 2.0 * (p.ny + 2 * reach + 1);
+    return segs;
+}
+
+// Rows of a strip of one form within time t: it computes 2 (steps - 1) rows beyond its own.
+inline int strip_rows(double t, int form, int steps)
+{
+    const int r = (int)(t / strip_row_cost(form)) - 2 * (steps - 1);
+    return r < 1 ? 1 : r;
+}
+
+// The least time (most: of a strip of that many rows) with count(time) <= slots, count falling with time.
+template <typename F> double strip_time(int steps, int most, int slots, const F &count)
+{
+    double lo = 2 * (steps - 1) + 1, hi = 2.0 * (most + 2 * (steps - 1) + 1);
     for (int i = 0; i < 40; i++) {
         const double mid = 0.5 * (lo + hi);
         if (count(mid) <= slots) hi = mid;
         else lo = mid;
     }
+    return hi;
+}
+
+// The strips of a lattice, at most `slots` of them if that can be: every strip takes about the same
+// time, so that strips resident together end together.  Sorted by rows, then columns.
+inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
+{
+    const std::vector<StripTile> segs = strip_segments(p);
+    const double t = strip_time(p.steps, p.ny, slots, [&](double t) {
+        long long n = 0;
+        for (const StripTile &s : segs) {
+            const int r = strip_rows(t, s.form, p.steps);
+            n += (s.y1 - s.y0 + r - 1) / r;
+        }
+        return n;
+    });
     std::vector<StripTile> out;
-    for (const Segment &s : segs) {
-        const int r = rows(hi, s.form), h = s.y1 - s.y0, n = (h + r - 1) / r;
+    for (const StripTile &s : segs) {
+        const int r = strip_rows(t, s.form, p.steps), h = s.y1 - s.y0, n = (h + r - 1) / r;
         for (int i = 0; i < n; i++)
             out.push_back({s.x0, s.y0 + (int)((long long)h * i / n), s.y0 + (int)((long long)h * (i + 1) / n), s.form});
     }
