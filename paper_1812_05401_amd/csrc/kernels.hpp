@@ -77,18 +77,18 @@ struct PatchShape {
 const PatchShape *patch_shape(int storage, long long nodes, long long most);
 
 // A form of the strip sweep: columns per lane, steps per launch, waves per SIMD, own columns of a
-// window and the halo beside them, and its launch: steps *t_base + t_off .. + steps - 1 over the device
-// table strips[n].
+// window and the halo beside them, rows of a strip to aim at (strip_slots), and its launch: steps
+// *t_base + t_off .. + steps - 1 over the device table strips[n].
 struct StripShape {
-    int cols, steps, waves, own, halo;
+    int cols, steps, waves, own, halo, rows;
     void (*launch)(const StepArgs &a, const StripTile *strips, int n, hipStream_t st);
 };
 // Nodes from which the sweep is taken (below, a launch is a strip's latency: 0.72-1.08 times the tiled
 // kernels' speed at 512 x 512 to 1024 x 768, 1.08-1.17 at 1024 x 1024), and from which the form with two
 // columns per lane is (at 2048 x 1024 its strips are still too short).  The stochastically rounded
-// formats, whose random bits make a recomputed node dearer, gain from more (0.9 times at 4096 x 1024,
-// 1.17-1.27 at 8192 x 2048).
-constexpr long long kStripLeast = 800000, kStripWide = 5LL << 19, kStripStochastic = 6LL << 20;
+// formats, whose random bits make a recomputed node dearer, gain from more (kStripStochastic, and
+// kStripStochasticB for bf16sr with one column per lane): see strip_f16.hip.
+constexpr long long kStripLeast = 800000, kStripWide = 5LL << 19, kStripStochastic = 6LL << 20, kStripStochasticB = 3LL << 20;
 const StripShape *strip_shape_f32(long long nodes);
 const StripShape *strip_shape_f16(int storage, long long nodes);
 const StripShape *strip_shape_f64(int storage, long long nodes);

@@ -96,7 +96,7 @@ int graph_chunk(int steps)
 const StripShape *strip_shape(int storage, long long nodes)
 {
     // tuning override: 0 the form of the largest lattices, 1 that of the smallest ones that take the sweep
-    if (const char *e = getenv("VPLBM_STRIP_SHAPE")) nodes = atoi(e) ? (storage == kF16SR || storage == kBF16SR ? kStripStochastic : kStripLeast) : 1LL << 30;
+    if (const char *e = getenv("VPLBM_STRIP_SHAPE")) nodes = atoi(e) ? (storage == kF16SR ? kStripStochastic : storage == kBF16SR ? kStripStochasticB : kStripLeast) : 1LL << 30;
     switch (storage) {
     case kF32: return strip_shape_f32(nodes);
     case kF64:
@@ -361,7 +361,7 @@ int ensure_strips(vplbm_sim s)
     if (!s->shape || s->nstrips) return VPLBM_OK;
     const StripPlan plan{s->g.nx, s->g.ny, s->g.xper != 0, s->g.yper != 0, 64 * s->shape->cols, s->shape->halo, s->shape->steps,
                          s->nsolid, s->solid_box};
-    int slots = strip_slots((long long)s->g.nx * s->g.ny, s->shape->own, 1024 * s->shape->waves);
+    int slots = strip_slots((long long)s->g.nx * s->g.ny, s->shape->own, 1024 * s->shape->waves, s->shape->rows);
     if (const char *e = getenv("VPLBM_STRIP_SLOTS")) slots = atoi(e);   // tuning override
     const std::vector<StripTile> list = plan_strips(plan, slots);
     const int n = (int)list.size();

@@ -256,13 +256,16 @@ __device__ __forceinline__ void round_cols(Cols<S, C> g[9], int c, const typenam
             }
         }
         if constexpr (S == kF16SR) {
-            // values below 2^-14 round on another quantum, and those near 2^16 to infinity
+            // Values below 2^-14 round on another quantum, and those near 2^16 to infinity.  In a wake every
+            // other wave holds one, where a population changes sign: each is looked at by itself.
             if (__ballot(least < 6.103515625e-05f || most >= 65472.0f) & lanes) {
                 r = r0;
 #pragma unroll
                 for (int k = 0; k < 9; k++) {
                     if (k % 2 == 0 && k > 0) r = xorshift32(r);
-                    up[k] = __float_as_uint((float)f16_stochastic(h[k], (k % 2) ? (r >> 16) : r));
+                    const float a = __builtin_fabsf(h[k]);
+                    if (__any(a < 6.103515625e-05f || a >= 65472.0f))
+                        up[k] = __float_as_uint((float)f16_stochastic(h[k], (k % 2) ? (r >> 16) : r));
                 }
             }
         }

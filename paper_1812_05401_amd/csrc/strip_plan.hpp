@@ -103,13 +103,13 @@ inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
 }
 
 // Strips to cut a lattice into: as many rounds of the `resident` waves that the GPU holds at once as
-// leave a strip about 36 rows (measured at 8192 x 2048 and 8192 x 8192: fewer, taller strips end less
-// evenly, more compute too many rows twice), and one round of three quarters of them where that makes
-// strips of under eight rows.
-inline int strip_slots(long long nodes, int own, int resident)
+// leave a strip about `rows` rows (36, measured at 8192 x 2048 and 8192 x 8192: fewer, taller strips end
+// less evenly, more compute too many rows twice), and one round of three quarters of them where that
+// makes strips of under eight rows.
+inline int strip_slots(long long nodes, int own, int resident, int rows)
 {
-    const double rounds = double(nodes) / own / 36.0 / resident;
-    if (rounds < 0.22) return resident * 3 / 4;
+    const double rounds = double(nodes) / own / rows / resident;
+    if (nodes < 0.22 * 36.0 * own * resident) return resident * 3 / 4;
     const int n = rounds < 0.4 ? 1 : (int)(rounds + 0.6);
     return (int)std::min<long long>((long long)resident * 39 / 40 * n, 1 << 20);
 }
