@@ -7,10 +7,10 @@ moments, penalization, collision, store, and the FP64 mass/force reductions.  Th
 workload is the 8192 x 2048 transversely oscillating cylinder (VP-MRT, FP32 storage, Zou-He
 inlet, outflow, free-slip walls, disk D = 96, Re = 300, mask and solid velocity rebuilt on the
 device every step).  Its two population buffers (1.2 GB) far exceed the 256 MB Infinity Cache, so
-the step streams from HBM and the line's `roofline` is an HBM figure.  The library runs three
-steps per launch (the intermediate steps kept in LDS); `two_steps_per_launch` and
-`one_step_per_launch` time the same workload with two steps per launch and with one, the
-memory-bound kernel.  Beside it the line carries `cache_resident` (the
+the step streams from HBM and the line's `roofline` is an HBM figure.  The library runs six steps
+per launch of it (a strip sweep, the intermediate steps in registers: it is bound by the vector
+ALUs); `two_steps_per_launch` and `one_step_per_launch` time the same workload with two steps per
+launch and with one, the memory-bound kernel.  Beside it the line carries `cache_resident` (the
 2048 x 512 cylinder wake, whose 75 MB of buffers fit in the cache: MLUPS only),
 `taylor_couette_128` (the 128 x 128 FP64 case, launch-bound: MLUPS only), `reduced_precision`
 (the 8192 x 2048 cylinder in every storage format), `paper_cylinder_re500` (the paper's
@@ -87,10 +87,30 @@ def measured_traffic(workload, storage, steps_per_launch=1):
     return ent and ent.get("bytes_per_launch")
 
 
-def time_workload(case, steps, warmup, storage=None, spl=3):
+def launch_form(case, tiled):
+    """(kernel, lattice updates per launch) that the library takes for `case`: the rules of
+    strip_f32.hip, strip_f16.hip, strip_f64.hip and patch.hip, else the tiled kernels' `tiled` updates."""
+    st, n = case.storage, case.nx * case.ny
+    wide, fp64 = n >= 5 << 19, st in ("f64", "f32d")
+    strip = {"f32": 6 if wide else 4, "f64": 5, "f32d": 4 if wide else 3, "f16s": 4, "bf16s": 4}.get(st, 0)
+    if n < 800000:
+        strip = 0
+    if st == "f16sr":
+        strip = 3 if n >= 6 << 20 else 0
+    if st == "bf16sr":
+        strip = 3 if n >= 6 << 20 else 4 if n >= 3 << 20 else 0
+    if n <= (799999 if st == "f32" else 650000):
+        return "vplbm::patch_kernel", next((k for m, k in ((24000, 8), (65536, 6), (98304, 5), (150000, 4)) if n <= m), 3 if fp64 else 4)
+    eb = {"f64": 8, "f32": 4, "f32d": 4}.get(st, 2)
+    if strip and case.ny >= strip and 9 * eb * case.ny * ((case.nx + 63) // 64 * 64) < 1 << 32:
+        return "vplbm::strip_kernel", strip
+    return {1: "vplbm::step_kernel", 2: "vplbm::step2_kernel", 3: "vplbm::step3_kernel"}[tiled], tiled
+
+
+def time_workload(case, steps, warmup, storage=None, spl=0):
     """Time `steps` steps of `case` after `warmup`, with at most `spl` steps per launch: 1 creates
-    the simulation with VPLBM_TWO_STEP=0, 2 with VPLBM_THREE_STEP=0; the library takes as many as
-    the case allows (three for binary32 storage, else two)."""
+    the simulation with VPLBM_TWO_STEP=0, 2 with VPLBM_THREE_STEP=0, 3 with neither strips nor
+    patches; 0: as many as the library takes for the case."""
     import torch
     from paper_1812_05401_amd import binding as B
     if storage:
@@ -100,7 +120,9 @@ def time_workload(case, steps, warmup, storage=None, spl=3):
     # reads as "use a stream of your own").
     stream = torch.cuda.Stream()
     torch.cuda.set_stream(stream)
-    want = {"VPLBM_TWO_STEP": "1" if spl >= 2 else "0", "VPLBM_THREE_STEP": "1" if spl >= 3 else "0"}
+    want = {"VPLBM_TWO_STEP": "0" if spl == 1 else "1", "VPLBM_THREE_STEP": "0" if spl in (1, 2) else "1"}
+    if spl == 3:
+        want.update(VPLBM_STRIP="0", VPLBM_PATCH="0")
     old = {k: os.environ.get(k) for k in want}
     os.environ.update(want)
     try:
@@ -112,7 +134,9 @@ def time_workload(case, steps, warmup, storage=None, spl=3):
             else:
                 os.environ[k] = v
     assert sim.stream == stream.cuda_stream
-    spl = sim.steps_per_launch
+    tiled = sim.steps_per_launch
+    kernel, spl = launch_form(case, tiled) if spl == 0 else (
+        {1: "vplbm::step_kernel", 2: "vplbm::step2_kernel", 3: "vplbm::step3_kernel"}[tiled], tiled)
     sim.step(warmup)
     torch.cuda.synchronize()
     ev0 = torch.cuda.Event(enable_timing=True)
@@ -143,7 +167,6 @@ def time_workload(case, steps, warmup, storage=None, spl=3):
     # updates of a launch, over the same launch time.  Above 1 for the multi-step kernels, which
     # move those bytes once per spl updates.
     per_update = bpu * spl * case.nodes / launch_s / 1e9
-    kernel = {1: "vplbm::step_kernel", 2: "vplbm::step2_kernel", 3: "vplbm::step3_kernel"}[spl]
     roof = {"bound": "hbm", "achieved": round(hbm, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(hbm / HBM_PEAK_GBS, 4),
             "traffic": measured_traffic(case.name, case.storage, spl),
@@ -482,7 +505,7 @@ def main():
                 ceil["us_per_launch"] / line["roofline"]["launch_us"], 4)
     if main_res["steps_per_launch"] >= 2:
         # the same workload with fewer steps per launch: one (the memory-bound kernel and its
-        # roofline) and, under three, two
+        # roofline) and two
         for spl, key in ((2, "two_steps_per_launch"), (1, "one_step_per_launch")):
             if spl >= main_res["steps_per_launch"]:
                 continue
@@ -521,11 +544,11 @@ def main():
         line["reduced_precision"] = {"workload": "cylinder_wake_8192x2048", **red}
         # the paper's own Re = 500 cylinder (6048 x 2016, SRT, convective outlet), FP32
         pcr = {}
-        for spl, key in ((3, "three_steps_per_launch"), (2, "two_steps_per_launch"),
-                         (1, "one_step_per_launch")):
+        for spl, key in ((0, "most_steps_per_launch"), (3, "three_steps_per_launch"),
+                         (2, "two_steps_per_launch"), (1, "one_step_per_launch")):
             r = time_workload(I.paper_cylinder_re500("f32"), 402, 42, spl=spl)
             pcr[key] = {k: r[k] for k in ("mlups", "ms_per_step", "steps_per_launch", "roofline")}
-            print(f"# paper_cylinder_re500 ({spl} per launch): {r['mlups']:.0f} MLUPS",
+            print(f"# paper_cylinder_re500 ({r['steps_per_launch']} per launch): {r['mlups']:.0f} MLUPS",
                   file=sys.stderr, flush=True)
         line["paper_cylinder_re500"] = {"workload": "paper_cylinder_re500", "storage": "f32", **pcr}
         # FP32 square channels from cache-resident to far beyond the 256 MB Infinity Cache

@@ -12,9 +12,10 @@ the digest of the kernel sources it was measured on.
     python3 -m paper_1812_05401_amd.counters trace DIR
 
 Each DIR is a `rocprofv3 --pmc ... -d DIR` output folder of one run (its .db files are found
-below it).  The step kernels of a run are `vplbm::step3_kernel` (three lattice updates per
-launch), `vplbm::step2_kernel` (two) and `vplbm::step_kernel` (one); per kernel the median over
-its dispatches is taken.
+below it).  The step kernels of a run are `vplbm::strip_kernel<S, C, K, W>` and
+`vplbm::patch_kernel<S, W, H, K, N>` (K lattice updates per launch), `vplbm::step3_kernel` (three),
+`vplbm::step2_kernel` (two) and `vplbm::step_kernel` (one); per kernel the median over its
+dispatches is taken (patches: of launches of all K steps, if a run has others they are fewer).
 """
 import argparse
 import glob
@@ -27,7 +28,9 @@ import statistics
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("kernels.hip", "lattice.hpp", "kernels.hpp", "runtime.hip")
+KERNEL_SOURCES = ("kernels.hip", "lattice.hpp", "kernels.hpp", "runtime.hip", "node.hpp", "reduce.hpp", "strip.hpp",
+                  "strip_kernel.hpp", "strip_plan.hpp", "strip_f32.hip", "strip_f16.hip", "strip_f64.hip", "patch.hpp",
+                  "patch.hip")
 
 
 def source_digest(csrc=None):
@@ -87,7 +90,10 @@ def step_kernels(vals, counter):
     for (k, c), vs in vals.items():
         if c != counter:
             continue
-        if k.startswith("vplbm::step3_kernel"):
+        many = re.match(r"vplbm::(?:strip_kernel<\d+, \d+|patch_kernel<\d+, \d+, \d+), (\d+)", k)
+        if many:
+            spl = int(many.group(1))
+        elif k.startswith("vplbm::step3_kernel"):
             spl = 3
         elif k.startswith("vplbm::step2_kernel"):
             spl = 2
@@ -236,7 +242,8 @@ def trace(folder):
     segs = []
     for name, _, dur, grid, *_ in disp:
         k = short(name)
-        if not k.startswith(("vplbm::step3_kernel", "vplbm::step2_kernel", "vplbm::step_kernel")):
+        if not k.startswith(("vplbm::strip_kernel", "vplbm::patch_kernel", "vplbm::step3_kernel", "vplbm::step2_kernel",
+                             "vplbm::step_kernel")):
             continue
         if segs and segs[-1][0] == (k, grid):
             segs[-1][1].append(dur / 1e3)
