@@ -66,12 +66,13 @@ hipError_t HostCopy::read(hipStream_t st, const void *dev, size_t n, void *const
     const char *src = static_cast<const char *>(dev);
     const size_t total = n * parts;
     // us, fresh pages, 1 / 2 / 4 / 8 threads: 1 MB 70 / 79 / 74 / 108 (512 KB slots); 4 MB 223 / 233 / 238 / 245
-    // and 642 / 457 / 396 / 336 without huge pages; 16 MB 1040 / 820 / 658 / 611 (2 MB slots) and 3859 /
-    // 2159 / 1542 / 1029.  A copy on the link takes about 18 us besides its bytes, so slots are large where
-    // there are enough of them.
-    const size_t slot = total < ((size_t)16 << 20) ? (size_t)512 << 10 : (size_t)2 << 20;
+    // and 642 / 457 / 396 / 336 without huge pages; 16 MB 1210 / 758 / 661 / 664 (1 MB slots), 1040 / 820 / 658 /
+    // 611 (2 MB), 850 / 784 / 793 / 799 (512 KB).  A copy on the link takes about 18 us besides its bytes, so
+    // slots are large where there are enough of them; but a pinned megabyte costs 50 us when it is first
+    // used (18.9 MB of fields for the first time 2.8 ms with 32 MB of slots), so few where one copy is short.
+    const size_t slot = total < ((size_t)8 << 20) ? (size_t)512 << 10 : total < ((size_t)64 << 20) ? (size_t)1 << 20 : (size_t)2 << 20;
     const size_t chunks = (total + slot - 1) / slot;
-    const int want = total < ((size_t)2 << 20) ? 1 : total < ((size_t)8 << 20) ? 4 : kThreads;
+    const int want = total < ((size_t)2 << 20) ? 1 : total < ((size_t)64 << 20) ? 4 : kThreads;
     const int threads = (int)std::min<size_t>(std::min(want, most_threads()), chunks);
     // short copies are as quick straight; pinned and device destinations are quicker so
     bool staged = total >= ((size_t)64 << 10);

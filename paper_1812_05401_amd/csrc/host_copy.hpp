@@ -9,7 +9,7 @@ namespace vplbm {
 // A copy straight into pageable memory runs at 10.8 GB/s (4.4 without huge pages), bound by one thread
 // that faults the pages in and copies, against 57 GB/s over the link into pinned memory.  Here up to
 // eight threads each take chunks through two pinned slots of their own, one on the link while the
-// other is copied out.  402 MB: 38.6 -> 10.5 ms (95 -> 18); 43 MB: 4.2 -> 1.3 ms; 1 MB: 0.49 -> 0.07 ms.
+// other is copied out.  402 MB: 38.6 -> 10.5 ms (95 -> 18); 43 MB: 4.2 -> 1.5 ms; 1 MB: 0.49 -> 0.07 ms.
 // The other direction gains nothing (the pages are there): 30 GB/s, against 40.
 //
 // An object serves one call at a time (as a handle does).  Its pinned memory, at most 32 MB, is

@@ -10,8 +10,8 @@ from paper_1812_05401_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-# nodes of 24 (fields) and 72 (populations) bytes: below and above 64 KB, 512 KB, 2, 8 and 16 MB
-SIZES = [(30, 29), (67, 41), (131, 167), (301, 291), (613, 571), (1201, 583)]
+# nodes of 24 (fields) and 72 (populations) bytes: below and above 64 KB, 512 KB, 2, 8 and 64 MB
+SIZES = [(30, 29), (67, 41), (131, 167), (301, 291), (613, 571), (1201, 583), (1601, 701)]
 
 
 def same(got, want):
