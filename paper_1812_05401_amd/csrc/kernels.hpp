@@ -82,6 +82,7 @@ const PatchShape *patch_shape(int storage, long long nodes, long long most);
 struct StripShape {
     int cols, steps, waves, own, halo, rows;
     void (*launch)(const StepArgs &a, const StripTile *strips, int n, hipStream_t st);
+    hipError_t (*load)();          // the kernel's code onto the device (else the first launch does it)
 };
 // Nodes from which the sweep is taken (below, a launch is a strip's latency: 0.72-1.08 times the tiled
 // kernels' speed at 512 x 512 to 1024 x 768, 1.08-1.17 at 1024 x 1024), and from which the form with two

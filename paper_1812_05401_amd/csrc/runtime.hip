@@ -379,6 +379,8 @@ int ensure_strips(vplbm_sim s)
         s->strip_cap = n;
     }
     HIP_TRY(hipMemcpyAsync(s->strips, order.data(), sizeof(StripTile) * n, hipMemcpyHostToDevice, s->stream));
+    // 0.6 ms once per process, here rather than in whichever later call first has enough steps
+    HIP_TRY(s->shape->load());
     HIP_TRY(hipStreamSynchronize(s->stream));   // the copy reads `order`
     s->nstrips = n;
     return VPLBM_OK;

@@ -54,9 +54,15 @@ template <int S, int C, int K, int W> void strip_launch(const StepArgs &a, const
     strip_kernel<S, C, K, W><<<dim3(all_blocks(a, n)), dim3(64), 0, st>>>(a, strips);
 }
 
+template <int S, int C, int K, int W> hipError_t strip_load()
+{
+    hipFuncAttributes attr;
+    return hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(&strip_kernel<S, C, K, W>));
+}
+
 template <int S, int C, int K, int W> constexpr StripShape strip_form(int rows = 36)
 {
-    return {C, K, W, strip_width<S, C, K>(), strip_halo<S, C, K>(), rows, &strip_launch<S, C, K, W>};
+    return {C, K, W, strip_width<S, C, K>(), strip_halo<S, C, K>(), rows, &strip_launch<S, C, K, W>, &strip_load<S, C, K, W>};
 }
 
 }  // namespace vplbm
