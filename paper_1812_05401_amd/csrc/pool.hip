@@ -273,7 +273,9 @@ __device__ __forceinline__ void pool_residual_node(const PoolSim &d, int parity,
     d.snap[n + i] = uy;
 }
 
-// One workgroup per table entry; sums per tile or block (waves in a fixed order).
+// One workgroup per table entry; sums per tile or block (waves in a fixed order).  A simulation's check
+// goes through one table: that of its strips if it has them, whichever kernel advances it (a second pass
+// would compare the state with the snapshot that the first one just took).
 __global__ __launch_bounds__(kBlock2) void pool_residual_kernel(PoolSim *sims, const TileRef *tiles,
                                                                 const int *ntiles,
                                                                 const long long *t_base, int t_off)
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(kBlock2) void pool_residual_kernel(PoolSim *sims, c
     const TileRef tr = tiles[blockIdx.x];                     // the table is in XCD order
     const PoolSim &d = sims[tr.slot];
     const long long done = *t_base + t_off - d.t0;
-    if (!residual_due(d, done)) return;                       // uniform over the workgroup
+    if (!residual_due(d, done) || (d.tail && tr.kernel < kPoolStrips)) return;   // uniform over the workgroup
     const int x = tr.x0 + lane, width = tr.w;
     const int parity = pool_buf(d, done);
     const int rows = tr.kernel >= kPoolStrips ? pool_block_rows(tr.form) : tr.y1 - tr.y0;
