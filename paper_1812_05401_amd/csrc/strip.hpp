@@ -522,7 +522,7 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
         load_row(FULL ? row_of(i, 0) : nearest(row_of(i, 0)), next, full);
         if constexpr (GENERAL) {
 #pragma unroll
-            for (int k = 0; k < K; k++) next_ids[k] = load_ids(k, FULL ? row_of(i, k) : nearest(row_of(i, k)));
+            for (int k = 0; k < K; k++) next_ids[k] = load_ids(k, FULL ? row_of(i, k) : strip_id_row(job.y0, K, i, k, g.ny, g.yper));
         }
     };
     auto sweep_row = [&](int i, auto full) __attribute__((always_inline)) {

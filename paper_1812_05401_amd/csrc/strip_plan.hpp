@@ -1,5 +1,5 @@
-// How a lattice is cut into the strips of a strip sweep (host only, no device code), kept apart from
-// the runtime so it can be checked on its own.
+// How a lattice is cut into the strips of a strip sweep, and which mask rows a strip reads (plain C++,
+// no device code), kept apart from the runtime so it can be checked on its own.
 #pragma once
 
 #include <algorithm>
@@ -100,6 +100,17 @@ inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
         return a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0;
     });
     return out;
+}
+
+// The mask row that step k (of 0 .. steps - 1) loads in iteration i of a strip whose first own row is y0.
+// The step begins in iteration 2 k, on row y0 - (steps - 1) + k; before that its ids are not used, and
+// its row may lie more than a lattice of few rows below row 0, so it takes the strip's first row.  That
+// one and every later row wrap once at most where ny >= steps.
+constexpr int strip_id_row(int y0, int steps, int i, int k, int ny, bool yper)
+{
+    const int y = y0 - (steps - 1) + (i > k ? i - k : 0);
+    if (yper) return y < 0 ? y + ny : y >= ny ? y - ny : y;
+    return y < 0 ? 0 : y >= ny ? ny - 1 : y;
 }
 
 // Strips to cut a lattice into: as many rounds of the `resident` waves that the GPU holds at once as
