@@ -713,6 +713,7 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
         s->mask_all = m;
         s->mask = m + (want - 1) * mask_bytes;
         s->nmasks = want;
+        HIP_TRY(hipMemsetAsync(m, 0, want * mask_bytes, s->stream));   // the rows' padding, as at create
     }
     s->nsolid = nsolid;
     memcpy(s->solid_box, solid, sizeof solid);

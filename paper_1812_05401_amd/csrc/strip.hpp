@@ -352,13 +352,9 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
     bool at_in = false, at_out0 = false, at_out1 = false;   // (an inlet column is a lane's first: x = 0)
     if constexpr (GENERAL) {
         auto wrapped = [&](int x) __attribute__((always_inline)) { x %= g.nx; return x < 0 ? x + g.nx : x; };
-        if (g.xper) {
-            x0 = wrapped(ux);
-            x1 = C == 2 ? (x0 + 1 == g.nx ? 0 : x0 + 1) : x0;
-        } else {
-            x0 = ux < 0 ? 0 : (ux > g.nx - 1 ? (g.nx - 1) & ~(C - 1) : ux);
-            x1 = x0 + C - 1;
-        }
+        x0 = strip_column(ux, C, g.nx, g.xper);
+        if (g.xper) x1 = C == 2 ? (x0 + 1 == g.nx ? 0 : x0 + 1) : x0;
+        else x1 = x0 + C - 1;
         own1 = own0 && ux + C - 1 < g.nx;
         own0 = own0 && ux < g.nx;
         at_in = g.inlet && ux == 0;
@@ -401,7 +397,7 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
         const uint8_t *m = job.mask + k * job.mask_step + (size_t)y * g.pitch;
         if (C == 1) return m[unsigned(x0)];
         if (split) return unsigned(m[unsigned(x0)]) | unsigned(m[unsigned(x1)]) << 8;
-        return *reinterpret_cast<const unsigned short *>(m + unsigned(x0));
+        return strip_ids(*reinterpret_cast<const unsigned short *>(m + unsigned(x0)), x1, g.nx);
     };
     // p seen from the left neighbour's column; the last column before an outlet sees its own
     auto from_right = [&](const P &p) __attribute__((always_inline)) -> P {

@@ -113,6 +113,18 @@ constexpr int strip_id_row(int y0, int steps, int i, int k, int ny, bool yper)
     return y < 0 ? 0 : y >= ny ? ny - 1 : y;
 }
 
+// The lattice column of a lane whose first column is ux: the wrapped one, or beyond a non-periodic edge
+// the nearest inside that a load of `cols` columns may start at.
+constexpr int strip_column(int ux, int cols, int nx, bool xper)
+{
+    if (xper) return ux % nx < 0 ? ux % nx + nx : ux % nx;
+    return ux < 0 ? 0 : ux > nx - 1 ? (nx - 1) / cols * cols : ux;
+}
+
+// The ids of a lane's two columns, loaded together: where the second (x1) lies beyond the last column of
+// an odd lattice, the byte is the row's padding and stands for no body.
+constexpr unsigned strip_ids(unsigned pair, int x1, int nx) { return x1 < nx ? pair : pair & 0xFFu; }
+
 // Strips to cut a lattice into: as many rounds of the `resident` waves that the GPU holds at once as
 // leave a strip about `rows` rows (36, measured at 8192 x 2048 and 8192 x 8192: fewer, taller strips end
 // less evenly, more compute too many rows twice), and one round of three quarters of them where that

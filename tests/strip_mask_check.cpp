@@ -1,13 +1,37 @@
-// Mask rows of the strip sweep (strip_id_row): inside the lattice for every strip of every lattice of
-// `steps` rows and up, and the row of the step once the step has begun.  Prints "ok", or the first fault.
+// What the strip sweep reads of a mask.  Rows (strip_id_row): inside the lattice for every strip of every
+// lattice of `steps` rows and up, and the row of the step once the step has begun.  Columns (strip_column,
+// strip_ids): of a row whose padding holds anything, only ids of the lattice's columns come through.
+// Prints "ok", or the first fault.
 #include <cstdio>
+#include <vector>
 
 #include "strip_plan.hpp"
 
 using namespace vplbm;
 
+static bool columns()
+{
+    for (int nx = 3; nx <= 300; nx++)
+        for (int per = 0; per < (nx & 1 ? 1 : 2); per++) {   // (an odd periodic lattice takes two loads)
+            std::vector<unsigned char> row((nx + 63) / 64 * 64, 0xEE);
+            for (int x = 0; x < nx; x++) row[x] = (unsigned char)(x % 9);
+            for (int ux = -6; ux < nx + 128; ux += 2) {
+                const int x0 = strip_column(ux, 2, nx, per != 0), x1 = x0 + 1;
+                const bool inside = x0 >= 0 && x0 < nx && x1 < (int)row.size() && x0 % 2 == 0;
+                const unsigned ids = inside ? strip_ids(row[x0] | row[x1] << 8, x1, nx) : 0u;
+                const unsigned want = inside ? x0 % 9 | (x1 < nx ? x1 % 9 << 8 : 0) : 1u;
+                if (ids != want) {
+                    std::printf("nx %d periodic %d column %d: ids %x\n", nx, per, ux, ids);
+                    return false;
+                }
+            }
+        }
+    return true;
+}
+
 int main()
 {
+    if (!columns()) return 1;
     for (int steps = 1; steps <= 8; steps++)
         for (int ny = steps < 3 ? 3 : steps; ny <= 24; ny++)
             for (int per = 0; per < 2; per++)
