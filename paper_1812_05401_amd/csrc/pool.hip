@@ -495,6 +495,7 @@ struct vplbm_pool_s {
     int64_t next_id = 0;
     uint64_t used = 0;
     bool in_flight = false;
+    bool stale = false;                   // the device's tables are not those of h_sims (an upload is due)
     int32_t finished = 0;
     uint64_t max_nodes = 0;               // admission cap on resident lattice nodes (0: none)
     uint64_t resident_nodes = 0;
@@ -575,6 +576,7 @@ int retire(vplbm_pool p, int slot)
     const int state = r.obs.status ? VPLBM_FAILED : (cancelled ? VPLBM_CANCELLED : VPLBM_DONE);
     host_log("pool %p: retire request %lld (%s) after %lld steps", (void *)p, (long long)r.id,
         state == VPLBM_DONE ? "done" : state == VPLBM_FAILED ? "failed" : "cancelled", done);
+    p->stale = true;                      // until the upload the device steps it still
     p->leaving.push_back({r.id, d, state});
     p->resident_nodes -= (uint64_t)r.cfg.nx * r.cfg.ny;
     r.slot = -1;
@@ -705,6 +707,7 @@ int admit(vplbm_pool p, Request &r, int slot)
     }
     // the body table copy above reads `hp` from the stack: let it land before returning
     HIP_TRY(hipStreamSynchronize(p->stream));
+    p->stale = true;
     p->h_sims[slot] = d;
     p->segments[slot] = std::move(segments);
     r.slot = slot;
@@ -906,6 +909,7 @@ int upload_tables(vplbm_pool p)
     HIP_TRY(hipMemcpyAsync(p->d_sims, p->h_sims.data(), sizeof(PoolSim) * p->cfg.max_slots, hipMemcpyHostToDevice, p->stream));
     // The host copies above read memory that changes on the next call: finish them.
     HIP_TRY(hipStreamSynchronize(p->stream));
+    p->stale = false;
     return VPLBM_OK;
 }
 
@@ -1076,7 +1080,6 @@ int vplbm_pool_advance(vplbm_pool p, int32_t *running, int32_t *queued, int32_t 
         p->t_host += p->cfg.steps_per_launch;
         HIP_TRY(hipMemcpy(p->h_sims.data(), p->d_sims, sizeof(PoolSim) * p->cfg.max_slots, hipMemcpyDeviceToHost));
     }
-    bool changed = false;
     for (int s = 0; s < p->cfg.max_slots; s++) {
         PoolSim &d = p->h_sims[s];
         if (!d.active) continue;
@@ -1085,7 +1088,6 @@ int vplbm_pool_advance(vplbm_pool p, int32_t *running, int32_t *queued, int32_t 
         if (done >= d.target || (d.status & 1u) || p->reqs[p->slot_req[s]].cancel) {
             int rc = retire(p, s);
             if (rc) return rc;
-            changed = true;
         }
     }
     // The retired simulations' fields take about 1 ms per 16 MB.  With requests waiting for the memory
@@ -1129,17 +1131,17 @@ int vplbm_pool_advance(vplbm_pool p, int32_t *running, int32_t *queued, int32_t 
             host_log("pool %p: request %lld failed: the device refused %llu bytes with nothing resident",
                 (void *)p, (long long)r.id, (unsigned long long)r.bytes);
             p->queue.pop_front();
-            changed = true;
             continue;
         }
         if (rc == 0) break;
         p->slot_req[slot] = r.id;
         p->queue.pop_front();
-        changed = true;
     }
     int nrun = 0;
     for (int s = 0; s < p->cfg.max_slots; s++) nrun += p->h_sims[s].active ? 1 : 0;
-    if (changed) {
+    // Also where an earlier call ended in an error before its upload: what it retired may have given its
+    // memory back since.
+    if (p->stale) {
         int rc = upload_tables(p);
         if (rc) return rc;
     }
