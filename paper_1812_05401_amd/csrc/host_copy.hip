@@ -74,8 +74,9 @@ hipError_t HostCopy::read(hipStream_t st, const void *dev, size_t n, void *const
     const size_t chunks = (total + slot - 1) / slot;
     const int want = total < ((size_t)2 << 20) ? 1 : total < ((size_t)64 << 20) ? 4 : kThreads;
     const int threads = (int)std::min<size_t>(std::min(want, most_threads()), chunks);
-    // short copies are as quick straight; pinned and device destinations are quicker so
-    bool staged = total >= ((size_t)64 << 10);
+    // short copies are as quick straight; pinned and device destinations are quicker so; hipStreamPerThread
+    // names another stream in each of the threads, which would not wait for the caller's work
+    bool staged = total >= ((size_t)64 << 10) && st != hipStreamPerThread;
     for (int i = 0; i < parts && staged; i++) {
         if (!dst[i]) continue;
         hipPointerAttribute_t attr{};
