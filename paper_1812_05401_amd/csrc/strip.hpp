@@ -397,7 +397,7 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
         const uint8_t *m = job.mask + k * job.mask_step + (size_t)y * g.pitch;
         if (C == 1) return m[unsigned(x0)];
         if (split) return unsigned(m[unsigned(x0)]) | unsigned(m[unsigned(x1)]) << 8;
-        return strip_ids(*reinterpret_cast<const unsigned short *>(m + unsigned(x0)), x1, g.nx);
+        return *reinterpret_cast<const unsigned short *>(m + unsigned(x0));
     };
     // p seen from the left neighbour's column; the last column before an outlet sees its own
     auto from_right = [&](const P &p) __attribute__((always_inline)) -> P {
@@ -467,7 +467,7 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
             // every lane takes the penalized form; at a fluid node its factors make it the fluid one
 #pragma unroll
             for (int c = 0; c < C; c++) {
-                const int id = int((ids >> (8 * c)) & 0xFFu);
+                const int id = strip_id(ids, c, x1, g.nx);
                 T usx = T(0), usy = T(0), fx, fy;
                 if (id) body_velocity(shared.body[k][id - 1], c ? x1 : x0, yw, usx, usy);
                 drho[c] = relax_solid(h[c], id != 0, usx, usy, rates, fx, fy);
@@ -508,17 +508,17 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
     const int n = job.y1 - job.y0 + 2 * (K - 1);
     auto row_of = [&](int i, int k) __attribute__((always_inline)) -> int { return yb + i - k; };   // row of step 1 + k
     auto inside = [&](int y) __attribute__((always_inline)) -> bool { return g.yper || (y >= 0 && y < g.ny); };
-    auto nearest = [&](int y) __attribute__((always_inline)) -> int { return g.yper ? wrap_row(y) : (y < 0 ? 0 : (y >= g.ny ? g.ny - 1 : y)); };
 
     P next[9];
     unsigned next_ids[K];
     // full (an integral constant): every step works, on rows clear of the lattice's first and last
     auto prefetch = [&](int i, auto full) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full)::value;
-        load_row(FULL ? row_of(i, 0) : nearest(row_of(i, 0)), next, full);
+        load_row(FULL ? row_of(i, 0) : strip_row(row_of(i, 0), g.ny, g.yper), next, full);
         if constexpr (GENERAL) {
 #pragma unroll
-            for (int k = 0; k < K; k++) next_ids[k] = load_ids(k, FULL ? row_of(i, k) : strip_id_row(job.y0, K, i, k, g.ny, g.yper));
+            for (int k = 0; k < K; k++)
+                next_ids[k] = FULL || strip_begun(i, k) ? load_ids(k, FULL ? row_of(i, k) : strip_row(row_of(i, k), g.ny, g.yper)) : 0u;
         }
     };
     auto sweep_row = [&](int i, auto full) __attribute__((always_inline)) {

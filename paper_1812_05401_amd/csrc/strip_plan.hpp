@@ -102,13 +102,14 @@ inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
     return out;
 }
 
-// The mask row that step k (of 0 .. steps - 1) loads in iteration i of a strip whose first own row is y0.
-// The step begins in iteration 2 k, on row y0 - (steps - 1) + k; before that its ids are not used, and
-// its row may lie more than a lattice of few rows below row 0, so it takes the strip's first row.  That
-// one and every later row wrap once at most where ny >= steps.
-constexpr int strip_id_row(int y0, int steps, int i, int k, int ny, bool yper)
+// Whether step k (of 0 .. steps - 1) works in iteration i of a strip, on row y0 - (steps - 1) + i - k.  Before
+// that its row may lie more than a lattice of few rows below row 0, where strip_row has no answer.
+constexpr bool strip_begun(int i, int k) { return i >= 2 * k; }
+
+// The row of the lattice that stands for row y of a strip: the wrapped one (rows that steps work on wrap
+// once at most where ny >= steps), or beyond a free-slip edge the nearest.
+constexpr int strip_row(int y, int ny, bool yper)
 {
-    const int y = y0 - (steps - 1) + (i > k ? i - k : 0);
     if (yper) return y < 0 ? y + ny : y >= ny ? y - ny : y;
     return y < 0 ? 0 : y >= ny ? ny - 1 : y;
 }
@@ -118,12 +119,14 @@ constexpr int strip_id_row(int y0, int steps, int i, int k, int ny, bool yper)
 constexpr int strip_column(int ux, int cols, int nx, bool xper)
 {
     if (xper) return ux % nx < 0 ? ux % nx + nx : ux % nx;
-    return ux < 0 ? 0 : ux > nx - 1 ? (nx - 1) / cols * cols : ux;
+    return ux < 0 ? 0 : ux > nx - 1 ? (nx - 1) & ~(cols - 1) : ux;
 }
 
-// The ids of a lane's two columns, loaded together: where the second (x1) lies beyond the last column of
-// an odd lattice, the byte is the row's padding and stands for no body.
-constexpr unsigned strip_ids(unsigned pair, int x1, int nx) { return x1 < nx ? pair : pair & 0xFFu; }
+// The id of column c of a lane whose ids, a byte each, were loaded together: where the second column (x1)
+// lies beyond the last of an odd lattice, its byte is the row's padding and stands for no body.  (Where
+// an id is used: made of the loaded ids it cost 1% of the sweep at 8192 x 2048, 26% at the load itself,
+// which then waits.)
+constexpr int strip_id(unsigned ids, int c, int x1, int nx) { return c == 0 ? int(ids & 0xFFu) : x1 < nx ? int(ids >> 8 & 0xFFu) : 0; }
 
 // Strips to cut a lattice into: as many rounds of the `resident` waves that the GPU holds at once as
 // leave a strip about `rows` rows (36, measured at 8192 x 2048 and 8192 x 8192: fewer, taller strips end

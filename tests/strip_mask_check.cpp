@@ -1,6 +1,6 @@
-// What the strip sweep reads of a mask.  Rows (strip_id_row): inside the lattice for every strip of every
-// lattice of `steps` rows and up, and the row of the step once the step has begun.  Columns (strip_column,
-// strip_ids): of a row whose padding holds anything, only ids of the lattice's columns come through.
+// What the strip sweep reads of a mask.  Rows (strip_begun, strip_row): inside the lattice for every strip
+// of every lattice of `steps` rows and up, and the row of the step.  Columns (strip_column,
+// strip_id): of a row whose padding holds anything, only ids of the lattice's columns come through.
 // Prints "ok", or the first fault.
 #include <cstdio>
 #include <vector>
@@ -18,10 +18,10 @@ static bool columns()
             for (int ux = -6; ux < nx + 128; ux += 2) {
                 const int x0 = strip_column(ux, 2, nx, per != 0), x1 = x0 + 1;
                 const bool inside = x0 >= 0 && x0 < nx && x1 < (int)row.size() && x0 % 2 == 0;
-                const unsigned ids = inside ? strip_ids(row[x0] | row[x1] << 8, x1, nx) : 0u;
-                const unsigned want = inside ? x0 % 9 | (x1 < nx ? x1 % 9 << 8 : 0) : 1u;
-                if (ids != want) {
-                    std::printf("nx %d periodic %d column %d: ids %x\n", nx, per, ux, ids);
+                const unsigned ids = inside ? row[x0] | row[x1] << 8 : 0u;
+                const int id0 = strip_id(ids, 0, x1, nx), id1 = strip_id(ids, 1, x1, nx);
+                if (!inside || id0 != x0 % 9 || id1 != (x1 < nx ? x1 % 9 : 0)) {
+                    std::printf("nx %d periodic %d column %d: ids %d %d\n", nx, per, ux, id0, id1);
                     return false;
                 }
             }
@@ -39,9 +39,9 @@ int main()
                     for (int y1 = y0 + 1; y1 <= ny; y1++)
                         for (int i = 0; i < y1 - y0 + 2 * (steps - 1); i++)
                             for (int k = 0; k < steps; k++) {
-                                const int row = strip_id_row(y0, steps, i, k, ny, per != 0);
-                                const int y = y0 - (steps - 1) + i - k;
-                                const bool used = i >= 2 * k && (per || (y >= 0 && y < ny));
+                                if (!strip_begun(i, k)) continue;
+                                const int y = y0 - (steps - 1) + i - k, row = strip_row(y, ny, per != 0);
+                                const bool used = per || (y >= 0 && y < ny);
                                 if (row < 0 || row >= ny || (used && row != (y + ny) % ny)) {
                                     std::printf("steps %d ny %d periodic %d strip %d..%d iteration %d step %d: row %d\n", steps, ny, per, y0, y1, i, k, row);
                                     return 1;
