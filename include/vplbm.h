@@ -134,7 +134,9 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
    earlier ones kept on chip (see vplbm_steps_per_launch); what remains of a call takes launches of
    fewer, and chunks of about 128 steps (whole launches) are replayed from a captured HIP graph (the
    environment variable VPLBM_GRAPH_STEPS at create sets another even chunk; 0 launches every step
-   directly).  Returns
+   directly).  A call of fewer steps than a chunk only launches kernels, so a caller may capture it on a
+   stream of its own; a capture of an even number of launches can be replayed, also after
+   vplbm_set_mask has set other bodies that do not move.  Returns
    VPLBM_EUNSTABLE if an earlier vplbm_observables saw status 1. */
 int vplbm_step(vplbm_sim s, int64_t nsteps);
 

@@ -11,6 +11,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <exception>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -129,8 +130,6 @@ struct vplbm_sim_s {
     bool device_mask = false;
     bool moving = false;
     int env_box[kMaxBodies][4];          // x0, y0, w, h swept by each moving body
-    int solid_box[kMaxBodies][4];        // boxes that hold every solid node at every time
-    int nsolid = 0;
     double *ring = nullptr;
     double *acc = nullptr;               // [kAccSets][kSub][kRingWidth] reduction sub-slots
     int ring_len = 0;
@@ -149,11 +148,14 @@ struct vplbm_sim_s {
     int graph_k = 0;
     bool two_step = true;                // two steps per launch where the case allows it
     bool three_step = true;              // three where the kernel exists for the case
-    bool strip = true;                   // four, by the strip sweep, where that exists
     const StripShape *shape = nullptr;   // form of the strip sweep, if there is one
-    StripTile *strips = nullptr;         // device table of the sweep's strips (xcd_entry order)
+    // Device table of the sweep's strips for the bodies that are set (xcd_entry order, empty ones last),
+    // and its host copy.  Of one length for any bodies, so that steps that a caller captured stay whole
+    // when the bodies change.
+    StripTile *strips = nullptr;
+    std::vector<StripTile> strip_list;
+    int nstrips = 0, strip_slots = 0;    // entries; strips that a plan aims at
     const PatchShape *patch = nullptr;   // form of the patch kernel, if the lattice is small
-    int nstrips = 0, strip_cap = 0;      // 0: to be built (ensure_strips)
     int64_t steps = 0;
     bool unstable = false;
     NodeParams params{};
@@ -269,14 +271,10 @@ bool three_step_ok(vplbm_sim s)
            s->buf_bytes <= 0xFFFFFFFFu && (!s->moving || s->nmasks >= 3);
 }
 
-// Steps per launch of the strip sweep for this simulation, 0: not taken.  Its buffer resources hold
-// 32-bit sizes, and a row of a periodic lattice wraps once at most.
+// Steps per launch of the strip sweep for this simulation, 0: not taken.
 int strip_k(vplbm_sim s)
 {
-    const int k = s->shape ? s->shape->steps : 0;
-    const bool ok = k && s->strip && s->two_step && s->three_step && s->buf_bytes <= 0xFFFFFFFFu &&
-                    s->g.ny >= k && (!s->moving || s->nmasks >= k);
-    return ok ? k : 0;
+    return s->shape && (!s->moving || s->nmasks >= s->shape->steps) ? s->shape->steps : 0;
 }
 
 // Steps per launch on patches in LDS, 0: not taken.
@@ -355,35 +353,28 @@ int mask_box(const Geom &g, const uint8_t *id, int box[4])
     return 1;
 }
 
-// The sweep's strips for the bodies that are set, in device memory: built before the first step on them.
-int ensure_strips(vplbm_sim s)
+// The sweep's table for bodies in the given boxes.
+int plan_table(vplbm_sim s, int nbox, const int (*box)[4], std::vector<StripTile> &table)
 {
-    if (!s->shape || s->nstrips) return VPLBM_OK;
-    const StripPlan plan{s->g.nx, s->g.ny, s->g.xper != 0, s->g.yper != 0, 64 * s->shape->cols, s->shape->halo, s->shape->steps,
-                         s->nsolid, s->solid_box};
-    int slots = strip_slots((long long)s->g.nx * s->g.ny, s->shape->own, 1024 * s->shape->waves, s->shape->rows);
-    if (const char *e = getenv("VPLBM_STRIP_SLOTS")) slots = atoi(e);   // tuning override
-    const std::vector<StripTile> list = plan_strips(plan, slots);
-    const int n = (int)list.size();
-    std::vector<StripTile> order(n);
-    for (int b = 0; b < n; b++) order[b] = list[xcd_entry(b, n)];
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    if (n > s->strip_cap) {
-        if (s->strips) HIP_TRY(hipFree(s->strips));
-        s->strips = nullptr;
-        s->strip_cap = 0;
-        if (hipMalloc(&s->strips, sizeof(StripTile) * n) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(VPLBM_ENOMEM, "cannot allocate the table of %d strips", n);
-        }
-        s->strip_cap = n;
+    if (!s->shape) return VPLBM_OK;
+    const StripPlan plan{s->g.nx, s->g.ny, s->g.xper != 0, s->g.yper != 0, 64 * s->shape->cols, s->shape->halo, s->shape->steps, nbox, box};
+    try {
+        const std::vector<StripTile> list = plan_strips(plan, s->strip_slots);
+        const int n = (int)list.size();
+        table.assign(s->nstrips, StripTile{0, 0, 0, kPlain});
+        for (int b = 0; b < n; b++) table.at(b) = list[xcd_entry(b, n)];
+    } catch (const std::exception &) {
+        return fail(VPLBM_ENOMEM, "cannot allocate the table of %d strips", s->nstrips);
     }
-    HIP_TRY(hipMemcpyAsync(s->strips, order.data(), sizeof(StripTile) * n, hipMemcpyHostToDevice, s->stream));
-    // 0.6 ms once per process, here rather than in whichever later call first has enough steps
-    HIP_TRY(s->shape->load());
-    HIP_TRY(hipStreamSynchronize(s->stream));   // the copy reads `order`
-    s->nstrips = n;
     return VPLBM_OK;
+}
+
+// The table onto the device; it stays as it is until a later call that waits for the stream.
+hipError_t place_table(vplbm_sim s, std::vector<StripTile> &table)
+{
+    if (!s->shape) return hipSuccess;
+    s->strip_list.swap(table);
+    return hipMemcpyAsync(s->strips, s->strip_list.data(), sizeof(StripTile) * s->nstrips, hipMemcpyHostToDevice, s->stream);
 }
 
 int ensure_graph(vplbm_sim s, int parity)
@@ -425,7 +416,7 @@ void release(vplbm_sim s)
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (int p = 0; p < 2; p++)
         if (s->graph[p]) (void)hipGraphExecDestroy(s->graph[p]);
-    void *ptrs[] = {s->buf[0], s->buf[1], s->mask_all, s->small, s->strips, s->staging, s->snap, s->rpart};
+    void *ptrs[] = {s->buf[0], s->buf[1], s->mask_all, s->small, s->staging, s->snap, s->rpart};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
@@ -584,7 +575,15 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     if (const char *e = getenv("VPLBM_NT_STORE")) s->nt_store = atoi(e) ? 1 : 0;
     if (const char *e = getenv("VPLBM_TWO_STEP")) s->two_step = atoi(e) != 0;   // 0: one step per launch
     if (const char *e = getenv("VPLBM_THREE_STEP")) s->three_step = atoi(e) != 0; // 0: at most two
-    if (const char *e = getenv("VPLBM_STRIP")) s->strip = atoi(e) != 0;           // 0: no strip sweep
+    // The strip sweep's buffer resources hold 32-bit sizes, and a row of a periodic lattice wraps once.
+    bool sweep = s->two_step && s->three_step && s->buf_bytes <= 0xFFFFFFFFu;
+    if (const char *e = getenv("VPLBM_STRIP")) sweep = sweep && atoi(e) != 0;     // 0: no strip sweep
+    if (s->shape && (!sweep || g.ny < s->shape->steps)) s->shape = nullptr;
+    if (s->shape) {
+        s->strip_slots = strip_slots((long long)g.nx * g.ny, s->shape->own, 1024 * s->shape->waves, s->shape->rows);
+        if (const char *e = getenv("VPLBM_STRIP_SLOTS")) s->strip_slots = atoi(e);   // tuning override
+        s->nstrips = strip_entries(g.nx, g.ny, s->shape->own, kMaxBodies, s->strip_slots);
+    }
     // the small arrays share one allocation, zeroed at once; each starts at a multiple of 256 bytes
     struct { void **p; size_t n; } smalls[] = {
         {(void **)&s->d_params, sizeof(BodyParams) * kMaxBodies},
@@ -595,6 +594,7 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
         {(void **)&s->ring, sizeof(double) * kRingWidth * s->ring_len},
         {&s->outlet[0], cfg->bc_xhi == VPLBM_CONVECTIVE ? sizeof(double) * 3 * g.ny : 0},
         {&s->outlet[1], cfg->bc_xhi == VPLBM_CONVECTIVE ? sizeof(double) * 3 * g.ny : 0},
+        {(void **)&s->strips, sizeof(StripTile) * s->nstrips},
     };
     size_t small_bytes = 0;
     for (auto &a : smalls) small_bytes += (a.n + 255) / 256 * 256;
@@ -627,6 +627,15 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     if (e == hipSuccess) e = launch_init(s->storage, step_args(s, 1, 0), nullptr, nullptr, nullptr, cfg->rho0, cfg->ux0, cfg->uy0, s->stream);
     s->cur = 0;
     if (e == hipSuccess) e = reset_outlet(s);
+    std::vector<StripTile> table;
+    rc = plan_table(s, 0, nullptr, table);
+    if (rc) {
+        release(s);
+        return rc;
+    }
+    if (e == hipSuccess) e = place_table(s, table);
+    // 0.6 ms once per process, here rather than in whichever later call first has enough steps
+    if (e == hipSuccess && s->shape) e = s->shape->load();
     if (e != hipSuccess) {
         release(s);
         return fail(VPLBM_EHIP, "initialisation failed: %s", hipGetErrorString(e));
@@ -664,6 +673,13 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
         for (size_t i = 0; i < n; i++)
             if (body_id[i] > nbodies) return fail(VPLBM_EINVAL, "body_id[%zu] = %d but only %d bodies", i, body_id[i], nbodies);
     }
+    int nsolid = 0, solid[kMaxBodies][4] = {};
+    if (body_id) nsolid = mask_box(g, body_id, solid[0]);
+    else
+        for (int k = 0; k < nbodies; k++) nsolid += body_box(g, bodies[k], solid[nsolid]);
+    std::vector<StripTile> table;
+    rc = plan_table(s, nsolid, solid, table);
+    if (rc) return rc;
     // The graphs hold pointers only, but moving-body nodes are part of them: rebuild lazily.
     HIP_TRY(hipStreamSynchronize(s->stream));
     for (int p = 0; p < 2; p++)
@@ -671,11 +687,8 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
             HIP_TRY(hipGraphExecDestroy(s->graph[p]));
             s->graph[p] = nullptr;
         }
-    int nsolid = 0, solid[kMaxBodies][4] = {};
-    if (body_id) nsolid = mask_box(g, body_id, solid[0]);
     for (int k = 0; k < nbodies; k++) {
         const vplbm_body &b = bodies[k];
-        if (!body_id) nsolid += body_box(g, b, solid[nsolid]);
         BodyParams &p = s->h_params[k];
         p.kind = b.kind; p.cx = b.cx; p.cy = b.cy; p.r = b.r; p.hx = b.hx; p.hy = b.hy;
         p.ux = b.ux; p.uy = b.uy; p.omega = b.omega; p.ax = b.ax; p.ay = b.ay; p.freq = b.freq;
@@ -702,8 +715,8 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
     // Moving bodies: every step of a launch takes a mask of its own.
     const size_t mask_bytes = (size_t)g.pitch * g.ny;
     if (moving && s->nmasks == 1) {
-        const bool many = s->two_step && s->three_step, sweep = many && s->strip && s->shape && s->buf_bytes <= 0xFFFFFFFFu;
-        const int want = many && s->patch ? s->patch->steps : sweep ? s->shape->steps : step3_supported(s->storage) ? 3 : 2;
+        const bool many = s->two_step && s->three_step;
+        const int want = many && s->patch ? s->patch->steps : s->shape ? s->shape->steps : step3_supported(s->storage) ? 3 : 2;
         uint8_t *m = nullptr;
         if (hipMalloc(&m, want * mask_bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -715,12 +728,10 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
         s->nmasks = want;
         HIP_TRY(hipMemsetAsync(m, 0, want * mask_bytes, s->stream));   // the rows' padding, as at create
     }
-    s->nsolid = nsolid;
-    memcpy(s->solid_box, solid, sizeof solid);
     s->nbodies = nbodies;
     s->moving = moving;
     s->device_mask = body_id == nullptr;
-    s->nstrips = 0;
+    HIP_TRY(place_table(s, table));
     if (nbodies) HIP_TRY(hipMemcpyAsync(s->d_params, s->h_params, sizeof(BodyParams) * nbodies, hipMemcpyHostToDevice, s->stream));
     HIP_TRY(launch_bodies(s->d_params, s->d_state, nbodies, s->t_dev, 0, s->stream));
     if (body_id) {
@@ -750,10 +761,6 @@ int vplbm_step(vplbm_sim s, int64_t nsteps)
     if (!valid(s)) return fail(VPLBM_EINVAL, "invalid handle");
     if (nsteps < 0) return fail(VPLBM_EINVAL, "nsteps must be >= 0");
     if (s->unstable) return fail(VPLBM_EUNSTABLE, "the simulation became unstable (non-finite or non-positive density)");
-    if (nsteps > 0 && !patch_k(s) && strip_k(s)) {
-        int rc = ensure_strips(s);
-        if (rc) return rc;
-    }
     while (nsteps > 0) {
         const StepChunk c = next_chunk(nsteps, s->graph_k);
         if (c.graph) {

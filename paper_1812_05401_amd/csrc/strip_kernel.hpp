@@ -20,6 +20,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W))) void st
         return;
     }
     const StripTile tile = strips[blockIdx.x];
+    if (tile.y1 <= tile.y0) return;                    // an empty entry (uniform)
     if (a.reduce) {
         // a plain strip sums no force, and its mass goes to the first slot
         const int rows = tile.form == kPlain ? 1 : kForceSlots;

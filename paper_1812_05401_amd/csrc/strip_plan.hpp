@@ -18,7 +18,7 @@ struct StripPlan {
     bool xper, yper;
     int window, halo;        // columns of a window, and those on either side that are not its own
     int steps;               // per launch
-    int nbox;                // boxes (x0, y0, w, h) that hold every solid node at every time
+    int nbox;                // boxes (x0, y0, w, h) inside the lattice that hold every solid node at every time
     const int (*box)[4];
 };
 
@@ -100,6 +100,16 @@ inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
         return a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0;
     });
     return out;
+}
+
+// Entries that hold the strips of a lattice whatever its `boxes` boxes are: plan_strips makes at most
+// `slots` strips, or one of each segment if those are more.  Rows of a window that boxes reach form at
+// most one run per box and, across a periodic edge, one more at either end; between and beside them lie
+// the plain ones.
+inline int strip_entries(int nx, int ny, int own, int boxes, int slots)
+{
+    const long long segments = (long long)((nx + own - 1) / own) * std::min(ny, 2 * boxes + 5);
+    return (int)std::max<long long>(slots, segments);
 }
 
 // Whether step k (of 0 .. steps - 1) works in iteration i of a strip, on row y0 - (steps - 1) + i - k.  Before
