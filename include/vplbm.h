@@ -157,8 +157,9 @@ const char *vplbm_last_error(void);
 int vplbm_init_fields(vplbm_sim s, const double *rho, const double *ux, const double *uy);
 
 /* Copy the populations to / from a host FP64 array [9][ny][nx] (decoded from / encoded to the
-   storage format).  set also sets the step counter to `step` (checkpoint/resume).  Both
-   synchronize the stream. */
+   storage format).  set also sets the step counter to `step` (checkpoint/resume); the per-step
+   observables of the steps before that are still in the ring stay there, and those that are not
+   read 0.  Both synchronize the stream. */
 int vplbm_get_populations(vplbm_sim s, double *pop);
 int vplbm_set_populations(vplbm_sim s, const double *pop, int64_t step);
 

@@ -40,7 +40,7 @@ struct StepArgs {
     double *ring;            // [ring_len][kRingWidth] per-step observables
     double *acc;             // [kAccSets][kSub][kRingWidth] per-step partial sums
     unsigned *status;        // bit 0: non-finite or non-positive density seen
-    const long long *t_base; // step counter on the device
+    const long long *t_base; // on the device: the step counter, and the step of the last restart
     Geom g;
     Outlet outlet;           // convective outlet state (prev = nullptr: none)
     int t_off;               // this launch's step = *t_base + t_off

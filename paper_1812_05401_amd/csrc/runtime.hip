@@ -134,7 +134,7 @@ struct vplbm_sim_s {
     double *acc = nullptr;               // [kAccSets][kSub][kRingWidth] reduction sub-slots
     int ring_len = 0;
     unsigned *status = nullptr;
-    long long *t_dev = nullptr;
+    long long *t_dev = nullptr;          // steps done; the step of the last restart
     double *staging = nullptr;          // dense FP64 host<->device staging
     void *outlet[2] = {nullptr, nullptr}; // convective outlet state per buffer parity
     size_t staging_bytes = 0;
@@ -255,6 +255,27 @@ hipError_t reset_outlet(vplbm_sim s)
 {
     if (!s->outlet[0]) return hipSuccess;
     return launch_outlet_init(s->storage, step_args(s, s->cur, 0), s->outlet[s->cur], s->stream);
+}
+
+// The ring at a restart at `step`: it keeps the steps before that it holds, the last ones folded into it
+// first, and those that it does not hold (they were overwritten, or never done) read 0.
+hipError_t restart_series(vplbm_sim s, int64_t step)
+{
+    const int64_t len = s->ring_len, done = s->steps;
+    if (step > 0 && done > 0 && step > done - kMaxSteps) {
+        const hipError_t e = launch_fold(step_args(s, s->cur, 0), s->stream);
+        if (e != hipSuccess) return e;
+    }
+    int64_t t = step > len ? step - len : 0, end = step;
+    if (step > done) t = t > done ? t : done;
+    else end = done - len < step ? done - len : step;
+    while (t < end) {
+        const int64_t slot = t % len, run = end - t < len - slot ? end - t : len - slot;
+        const hipError_t e = launch_fill_f64(s->ring + slot * kRingWidth, (size_t)run * kRingWidth, 0.0, s->stream);
+        if (e != hipSuccess) return e;
+        t += run;
+    }
+    return hipSuccess;
 }
 
 // Two steps per launch: moving bodies take a second mask for the first step.
@@ -589,7 +610,7 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
         {(void **)&s->d_params, sizeof(BodyParams) * kMaxBodies},
         {(void **)&s->d_state_all, sizeof(BodyState) * kMaxBodies * kMaxSteps},
         {(void **)&s->status, sizeof(unsigned) * 4},
-        {(void **)&s->t_dev, sizeof(long long)},
+        {(void **)&s->t_dev, 2 * sizeof(long long)},
         {(void **)&s->acc, sizeof(double) * kAccSets * kSub * kRingWidth},
         {(void **)&s->ring, sizeof(double) * kRingWidth * s->ring_len},
         {&s->outlet[0], cfg->bc_xhi == VPLBM_CONVECTIVE ? sizeof(double) * 3 * g.ny : 0},
@@ -859,8 +880,9 @@ int vplbm_set_populations(vplbm_sim s, const double *pop, int64_t step)
     HIP_TRY(hipMemcpyAsync(s->staging, pop, 9 * n * sizeof(double), hipMemcpyHostToDevice, s->stream));
     HIP_TRY(launch_encode(s->storage, step_args(s, s->cur ^ 1, 0), s->staging, s->stream));
     HIP_TRY(reset_outlet(s));
-    long long t = step;
-    HIP_TRY(hipMemcpyAsync(s->t_dev, &t, sizeof t, hipMemcpyHostToDevice, s->stream));
+    if (s->cfg.reduce) HIP_TRY(restart_series(s, step));
+    const long long t[2] = {step, step};
+    HIP_TRY(hipMemcpyAsync(s->t_dev, t, sizeof t, hipMemcpyHostToDevice, s->stream));
     HIP_TRY(launch_fill_f64(s->acc, (size_t)kAccSets * kSub * kRingWidth, 0.0, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     s->steps = step;
