@@ -19,7 +19,7 @@ LIB = os.path.join(PKG, "libvplbm.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("kernels.hip", "runtime.hip", "pool.hip", "pool_strip.hip", "pool_strip_f64.hip", "pool_patch.hip", "static_scratch.hip", "host_copy.hip",
                                             "strip_f32.hip", "strip_f16.hip", "strip_f64.hip", "patch.hip")]
 HEADERS = [os.path.join(CSRC, f) for f in ("kernels.hpp", "lattice.hpp", "internal.hpp", "pool.hpp", "pool_strip.hpp", "pool_job.hpp", "patch.hpp", "pool_policy.hpp", "step_plan.hpp", "static_scratch.hpp", "reduce.hpp", "node.hpp", "strip.hpp", "strip_kernel.hpp", "strip_plan.hpp",
-                                            "host_copy.hpp")] + [
+                                            "host_copy.hpp", "side_by_side.hpp")] + [
     os.path.join(INCLUDE, "vplbm.h")]
 ARCH = os.environ.get("VPLBM_OFFLOAD_ARCH", "gfx950")
 # The probes: the step's access patterns with a trivial update, a copy, FMA chains (bench.py).

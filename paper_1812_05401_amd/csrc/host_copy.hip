@@ -4,26 +4,12 @@
 
 #include <algorithm>
 #include <atomic>
-#include <system_error>
-#include <thread>
+
+#include "side_by_side.hpp"
 
 namespace vplbm {
 
 namespace {
-
-// work(0) .. work(n - 1) side by side, all of them also where a thread cannot be started.
-template <typename F> void side_by_side(int n, const F &work)
-{
-    std::thread threads[8];
-    int started = 1;
-    try {
-        for (; started < n; started++) threads[started] = std::thread(work, started);
-    } catch (const std::system_error &) {
-    }
-    work(0);
-    for (int t = started; t < n; t++) work(t);
-    for (int t = 1; t < started; t++) threads[t].join();
-}
 
 int most_threads()
 {
