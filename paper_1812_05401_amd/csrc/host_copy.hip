@@ -4,6 +4,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <mutex>
+#include <new>
+#include <utility>
 
 #include "side_by_side.hpp"
 
@@ -17,34 +20,116 @@ int most_threads()
     return n < 1 ? 1 : n;
 }
 
+constexpr int kThreads = 8;
+
+// Pinned slots, and the events of the copies into them, of one device: two per thread.
+struct HostSlots {
+    int device;
+    char *pinned = nullptr;
+    size_t bytes = 0;
+    hipEvent_t event[2 * kThreads] = {};
+
+    explicit HostSlots(int d) : device(d) {}
+    ~HostSlots()
+    {
+        for (hipEvent_t e : event)
+            if (e) (void)hipEventDestroy(e);
+        if (pinned) (void)hipHostFree(pinned);
+    }
+
+    // room for n bytes and `slots` events; on the set's device
+    bool prepare(size_t n, int slots)
+    {
+        for (int i = 0; i < slots; i++)
+            if (!event[i] && hipEventCreateWithFlags(&event[i], hipEventDisableTiming) != hipSuccess) {
+                event[i] = nullptr;
+                (void)hipGetLastError();
+                return false;
+            }
+        if (bytes >= n) return true;
+        if (pinned) (void)hipHostFree(pinned);
+        pinned = nullptr;
+        bytes = 0;
+        if (hipHostMalloc((void **)&pinned, n, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            pinned = nullptr;
+            return false;
+        }
+        bytes = n;
+        return true;
+    }
+};
+
+// The sets that no read is using, for all objects of the process: a read takes one, or makes one where none
+// is left, and waits for nobody.  As many as reads have run at once, at most kIdle, and none once the last
+// object has gone.  (Each object kept its own once, 32 MB for good: a hundred handles held 3 GB.)
+constexpr int kIdle = 8;
+std::mutex g_mu;
+HostSlots *g_idle[kIdle];
+int g_nidle = 0, g_objects = 0;
+
+HostSlots *take(int device)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        for (int i = g_nidle - 1; i >= 0; i--)
+            if (g_idle[i]->device == device) {
+                HostSlots *s = g_idle[i];
+                g_idle[i] = g_idle[--g_nidle];
+                return s;
+            }
+    }
+    return new (std::nothrow) HostSlots(device);
+}
+
+void give(HostSlots *s)
+{
+    if (!s) return;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (g_nidle < kIdle) {
+            g_idle[g_nidle++] = s;
+            return;
+        }
+        // the larger ones stay
+        for (HostSlots *&o : g_idle)
+            if (o->bytes < s->bytes) std::swap(o, s);
+    }
+    delete s;
+}
+
+// The calling thread's device is this one (-1: its own) while this lives.
+struct OnDevice {
+    int before = -1;
+    explicit OnDevice(int device)
+    {
+        int now = device;
+        if (device >= 0 && hipGetDevice(&now) == hipSuccess && now != device && hipSetDevice(device) == hipSuccess) before = now;
+    }
+    ~OnDevice()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
 }  // namespace
+
+HostCopy::HostCopy()
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_objects++;
+}
 
 HostCopy::~HostCopy()
 {
-    for (hipEvent_t e : event_)
-        if (e) (void)hipEventDestroy(e);
-    if (pinned_) (void)hipHostFree(pinned_);
-}
-
-bool HostCopy::prepare(size_t bytes, int slots)
-{
-    for (int i = 0; i < slots; i++)
-        if (!event_[i] && hipEventCreateWithFlags(&event_[i], hipEventDisableTiming) != hipSuccess) {
-            event_[i] = nullptr;
-            (void)hipGetLastError();
-            return false;
-        }
-    if (bytes_ >= bytes) return true;
-    if (pinned_) (void)hipHostFree(pinned_);
-    pinned_ = nullptr;
-    bytes_ = 0;
-    if (hipHostMalloc((void **)&pinned_, bytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        pinned_ = nullptr;
-        return false;
+    HostSlots *last[kIdle];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (--g_objects == 0)
+            while (g_nidle > 0) last[n++] = g_idle[--g_nidle];
     }
-    bytes_ = bytes;
-    return true;
+    while (n > 0) delete last[--n];
 }
 
 hipError_t HostCopy::read(hipStream_t st, const void *dev, size_t n, void *const *dst, int parts)
@@ -69,9 +154,16 @@ hipError_t HostCopy::read(hipStream_t st, const void *dev, size_t n, void *const
         if (hipPointerGetAttributes(&attr, dst[i]) == hipSuccess) staged = attr.type == hipMemoryTypeUnregistered;
         else (void)hipGetLastError();
     }
-    int device = 0;
-    if (staged) staged = hipGetDevice(&device) == hipSuccess && prepare(2 * threads * std::min(slot, total), 2 * threads);
-    if (!staged) {
+    int device = -1;                     // an event belongs to the stream's device, whichever is current
+    if (staged && hipStreamGetDevice(st, &device) != hipSuccess) {
+        (void)hipGetLastError();
+        staged = false;
+        device = -1;
+    }
+    const OnDevice on(device);
+    HostSlots *const slots = staged ? take(device) : nullptr;
+    if (!slots || !slots->prepare(2 * threads * std::min(slot, total), 2 * threads)) {
+        give(slots);
         for (int i = 0; i < parts; i++)
             if (dst[i]) {
                 const hipError_t e = hipMemcpyAsync(dst[i], src + i * n, n, hipMemcpyDeviceToHost, st);
@@ -104,21 +196,22 @@ hipError_t HostCopy::read(hipStream_t st, const void *dev, size_t n, void *const
             while (next < chunks && !wanted(next)) next += threads;
             held[s] = next;
             if (next >= chunks || e != hipSuccess) return;
-            e = hipMemcpyAsync(pinned_ + (2 * t + s) * std::min(slot, total), src + next * slot, length(next), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess) e = hipEventRecord(event_[2 * t + s], st);
+            e = hipMemcpyAsync(slots->pinned + (2 * t + s) * std::min(slot, total), src + next * slot, length(next), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipEventRecord(slots->event[2 * t + s], st);
             next += threads;
         };
         fetch(0);
         fetch(1);
         for (int s = 0; held[s] < chunks && e == hipSuccess; s ^= 1) {
-            e = hipEventSynchronize(event_[2 * t + s]);
+            e = hipEventSynchronize(slots->event[2 * t + s]);
             if (e != hipSuccess) break;
-            deliver(held[s], pinned_ + (2 * t + s) * std::min(slot, total));
+            deliver(held[s], slots->pinned + (2 * t + s) * std::min(slot, total));
             fetch(s);
         }
         if (e != hipSuccess) error = e;
     });
     const hipError_t e = hipStreamSynchronize(st);   // no copy is under way when the slots are used again
+    give(slots);
     return error != hipSuccess ? (hipError_t)error.load() : e;
 }
 

@@ -12,25 +12,19 @@ namespace vplbm {
 // other is copied out.  402 MB: 38.6 -> 10.5 ms (95 -> 18); 43 MB: 4.2 -> 1.5 ms; 1 MB: 0.49 -> 0.07 ms.
 // The other direction gains nothing (the pages are there): 30 GB/s, against 40.
 //
-// An object serves one call at a time (as a handle does).  Its pinned memory, at most 32 MB, is
-// allocated at the first copy that needs it and goes with the object.
+// An object serves one call at a time (as a handle does), several objects several at once.  The pinned
+// memory, at most 32 MB a call, is shared: it is allocated where a copy finds none idle, and goes with the
+// last object of the process.
 class HostCopy {
 public:
-    HostCopy() = default;
+    HostCopy();
+    ~HostCopy();
     HostCopy(const HostCopy &) = delete;
     HostCopy &operator=(const HostCopy &) = delete;
-    ~HostCopy();
 
     // n bytes from dev + i * n to dst[i], for each dst[i] that is not null (parts of them), after the
     // work before it on the stream; done when it returns hipSuccess.
     hipError_t read(hipStream_t st, const void *dev, size_t n, void *const *dst, int parts);
-
-private:
-    static constexpr int kThreads = 8;
-    char *pinned_ = nullptr;
-    size_t bytes_ = 0;
-    hipEvent_t event_[2 * kThreads] = {};
-    bool prepare(size_t bytes, int slots);
 };
 
 // memcpy between host arrays, by several threads where that is worth their start.
