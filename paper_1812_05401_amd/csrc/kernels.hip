@@ -448,6 +448,20 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
 
 __global__ void fold_kernel(StepArgs a) { fold_recent(a, *a.t_base, blockIdx.x); }
 
+__global__ __launch_bounds__(kBlock) void unfold_kernel(StepArgs a)
+{
+    const int d = threadIdx.x / kRingWidth, q = threadIdx.x % kRingWidth;
+    const long long t = *a.t_base - 1 - d;
+    if (d < kMaxSteps && d < a.ring_len && t >= 0) acc_set(a, t)[q] = a.ring[(size_t)(t % a.ring_len) * kRingWidth + q];
+}
+
+hipError_t launch_unfold(const StepArgs &a, hipStream_t st)
+{
+    static_assert(kMaxSteps * kRingWidth <= kBlock, "a thread per value");
+    unfold_kernel<<<1, kBlock, 0, st>>>(a);
+    return hipGetLastError();
+}
+
 hipError_t launch_fold(const StepArgs &a, hipStream_t st)
 {
     fold_kernel<<<kRingWidth, 64, 0, st>>>(a);

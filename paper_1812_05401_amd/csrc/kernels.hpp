@@ -40,7 +40,7 @@ struct StepArgs {
     double *ring;            // [ring_len][kRingWidth] per-step observables
     double *acc;             // [kAccSets][kSub][kRingWidth] per-step partial sums
     unsigned *status;        // bit 0: non-finite or non-positive density seen
-    const long long *t_base; // on the device: the step counter, and the step of the last restart
+    const long long *t_base; // step counter on the device
     Geom g;
     Outlet outlet;           // convective outlet state (prev = nullptr: none)
     int t_off;               // this launch's step = *t_base + t_off
@@ -148,6 +148,9 @@ hipError_t launch_momentum_exchange(int storage, const StepArgs &a, double *out,
 hipError_t launch_outlet_init(int storage, const StepArgs &a, void *prev, hipStream_t st);
 // Sum the sub-slots of steps *t_base - 2 and *t_base - 1 into their ring entries.
 hipError_t launch_fold(const StepArgs &a, hipStream_t st);
+// After a restart at step *t_base, all sets cleared: the ring entries of the kMaxSteps steps before into their
+// sets, from which the next folds write them again.
+hipError_t launch_unfold(const StepArgs &a, hipStream_t st);
 hipError_t launch_fill_f64(double *p, size_t n, double v, hipStream_t st);
 hipError_t launch_fill_u32(unsigned *p, size_t n, unsigned v, hipStream_t st);
 

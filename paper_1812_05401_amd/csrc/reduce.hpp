@@ -12,18 +12,16 @@ __device__ __forceinline__ double *acc_set(const StepArgs &a, long long t)
     return a.acc + (size_t)(t & (kAccSets - 1)) * kSub * kRingWidth;
 }
 
-// Sum value q of the sub-slots of steps t - kMaxSteps .. t - 1 (those since the start or the last
-// restart, a.t_base[1]: the sets of those before are cleared) into their ring entries, with one wave:
-// lane l adds sub-slots l, l + 64, ... in order, then a fixed butterfly adds the lanes, so a result does
-// not depend on which workgroup folds or when.  One memory round trip for all of them.  Nothing is
-// cleared, so folding a step again gives the same value: a step is folded by the next launch, and again
-// by later ones while it is among their last kMaxSteps.
+// Sum value q of the sub-slots of steps t - kMaxSteps .. t - 1 (those that exist) into their ring
+// entries, with one wave: lane l adds sub-slots l, l + 64, ... in order, then a fixed butterfly
+// adds the lanes, so a result does not depend on which workgroup folds or when.  One memory round
+// trip for all of them.  Nothing is cleared, so folding a step again gives the same value: a step
+// is folded by the next launch, and again by later ones while it is among their last kMaxSteps.
 // The fold always takes the shuffle form of the wave sum, so that every fold of a step (by any
 // kernel class, or by an observation) writes the same value.
 __device__ __forceinline__ void fold_recent(const StepArgs &a, long long t, int q)
 {
     const int lane = threadIdx.x & 63;
-    const long long first = a.t_base[1];
     double v[kMaxSteps];
 #pragma unroll
     for (int d = 0; d < kMaxSteps; d++) v[d] = 0.0;
@@ -34,7 +32,7 @@ __device__ __forceinline__ void fold_recent(const StepArgs &a, long long t, int 
 #pragma unroll
     for (int d = 0; d < kMaxSteps; d++) {
         const double sum = wave_sum<false>(v[d]);
-        if (lane == 0 && t - 1 - d >= first && d < a.ring_len) a.ring[(size_t)((t - 1 - d) % a.ring_len) * kRingWidth + q] = sum;
+        if (lane == 0 && t >= 1 + d && d < a.ring_len) a.ring[(size_t)((t - 1 - d) % a.ring_len) * kRingWidth + q] = sum;
     }
 }
 

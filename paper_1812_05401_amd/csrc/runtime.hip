@@ -134,7 +134,7 @@ struct vplbm_sim_s {
     double *acc = nullptr;               // [kAccSets][kSub][kRingWidth] reduction sub-slots
     int ring_len = 0;
     unsigned *status = nullptr;
-    long long *t_dev = nullptr;          // steps done; the step of the last restart
+    long long *t_dev = nullptr;
     double *staging = nullptr;          // dense FP64 host<->device staging
     void *outlet[2] = {nullptr, nullptr}; // convective outlet state per buffer parity
     size_t staging_bytes = 0;
@@ -257,7 +257,7 @@ hipError_t reset_outlet(vplbm_sim s)
     return launch_outlet_init(s->storage, step_args(s, s->cur, 0), s->outlet[s->cur], s->stream);
 }
 
-// The ring at a restart at `step`: it keeps the steps before that it holds, the last ones folded into it
+// The ring before a restart at `step`: it keeps the steps before that it holds, the last ones folded into it
 // first, and those that it does not hold (they were overwritten, or never done) read 0.
 hipError_t restart_series(vplbm_sim s, int64_t step)
 {
@@ -610,7 +610,7 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
         {(void **)&s->d_params, sizeof(BodyParams) * kMaxBodies},
         {(void **)&s->d_state_all, sizeof(BodyState) * kMaxBodies * kMaxSteps},
         {(void **)&s->status, sizeof(unsigned) * 4},
-        {(void **)&s->t_dev, 2 * sizeof(long long)},
+        {(void **)&s->t_dev, sizeof(long long)},
         {(void **)&s->acc, sizeof(double) * kAccSets * kSub * kRingWidth},
         {(void **)&s->ring, sizeof(double) * kRingWidth * s->ring_len},
         {&s->outlet[0], cfg->bc_xhi == VPLBM_CONVECTIVE ? sizeof(double) * 3 * g.ny : 0},
@@ -881,9 +881,10 @@ int vplbm_set_populations(vplbm_sim s, const double *pop, int64_t step)
     HIP_TRY(launch_encode(s->storage, step_args(s, s->cur ^ 1, 0), s->staging, s->stream));
     HIP_TRY(reset_outlet(s));
     if (s->cfg.reduce) HIP_TRY(restart_series(s, step));
-    const long long t[2] = {step, step};
-    HIP_TRY(hipMemcpyAsync(s->t_dev, t, sizeof t, hipMemcpyHostToDevice, s->stream));
+    long long t = step;
+    HIP_TRY(hipMemcpyAsync(s->t_dev, &t, sizeof t, hipMemcpyHostToDevice, s->stream));
     HIP_TRY(launch_fill_f64(s->acc, (size_t)kAccSets * kSub * kRingWidth, 0.0, s->stream));
+    if (s->cfg.reduce && step > 0) HIP_TRY(launch_unfold(step_args(s, s->cur, 0), s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     s->steps = step;
     return VPLBM_OK;
