@@ -8,12 +8,12 @@ namespace vplbm {
 // A strip, or one of its blocks where the simulation ends (final_step), for KK <= K steps.
 template <int S, int K, int KK>
 __device__ __forceinline__ void pool_strip(const StripJob &job, int form, PoolSim *sim, int block, bool final_step,
-                                           StripShared<typename Codec<S>::real, K> &shared)
+                                           StripLastShared<typename Codec<S>::real, K> &shared)
 {
     using T = typename Codec<S>::real;
     constexpr int V = strip_width<S, 1, K>();
     const int lane = threadIdx.x;
-    for (int i = lane; i < KK * kForceSlots * kRingWidth; i += 64) (&shared.part[0][0][0])[i] = 0.0;
+    for (int i = lane; i < 64 * kRingWidth; i += 64) (&shared.part[0][0])[i] = 0.0;
     double mass[KK];
 #pragma unroll
     for (int k = 0; k < KK; k++) mass[k] = 0.0;
@@ -24,11 +24,11 @@ __device__ __forceinline__ void pool_strip(const StripJob &job, int form, PoolSi
     if (final_step) {
         const int w = job.g.nx - job.x0 < V ? job.g.nx - job.x0 : V;
         const double m = wave_sum<wave_sum_dpp<T>()>(mass[KK - 1]);
-        if (lane == 0) shared.part[KK - 1][0][0] = double(w) * double(job.y1 - job.y0) + m;
+        if (lane == 0) shared.part[0][0] = double(w) * double(job.y1 - job.y0) + m;
         __syncthreads();
         if (lane < kRingWidth) {
             double v = 0.0;
-            for (int q = 0; q < kForceSlots; q++) v += shared.part[KK - 1][q][lane];   // fixed order
+            for (int q = 0; q < 64; q++) v += shared.part[q][lane];   // fixed order
             sim->partials[(size_t)block * kRingWidth + lane] = v;
         }
         __syncthreads();
@@ -65,7 +65,7 @@ template <int S, int K, int W>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W))) void pool_strip_tail_kernel(PoolLaunch a)
 {
     using T = typename Codec<S>::real;
-    __shared__ StripShared<T, K> shared;
+    __shared__ StripLastShared<T, K> shared;
     const int n = *a.ntiles;
     const TileRef tr = a.tiles[blockIdx.x];
     if ((int)blockIdx.x >= n) return;

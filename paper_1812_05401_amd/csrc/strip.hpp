@@ -308,22 +308,34 @@ template <typename P> struct StripRows {
     P m2, m5, m6;                // row y, unshifted
 };
 
-// LDS of a strip.
+// LDS of a strip: sums; per step each body's centre, velocity and angular velocity, and the outlet records
+// of the last two rows, by row parity.
+//
+// With the sums of every step, mass and the force on every body: a lane adds to slot lane % kForceSlots, so
+// that at most four lanes of a wave meet at one address; in which order they are added is the hardware's
+// choice, so the last bits of a force are not fixed.
 constexpr int kForceSlots = 16;
 template <typename T, int K> struct StripShared {
-    // per step: mass, and the force on every body; a lane adds to slot lane % kForceSlots, so that at
-    // most four lanes of a wave meet at one address
+    static constexpr bool kEveryStep = true;
     double part[K][kForceSlots][kRingWidth];
-    T body[K][kMaxBodies][5];         // per step: each body's centre, velocity and angular velocity
-    T record[K][2][3];                // per step: outlet records of the last two rows, by row parity
+    T body[K][kMaxBodies][5];
+    T record[K][2][3];
+    __device__ __forceinline__ double *slot(int k, int lane) { return part[k][lane % kForceSlots]; }
+};
+// With the last step's alone: a slot per lane, each added to by its own lane only, row by row.
+template <typename T, int K> struct StripLastShared {
+    static constexpr bool kEveryStep = false;
+    double part[64][kRingWidth];
+    T body[K][kMaxBodies][5];
+    T record[K][2][3];
+    __device__ __forceinline__ double *slot(int, int lane) { return part[lane]; }
 };
 
 // K steps of one strip of windows laid out for KW.  mass: per step, this lane's sum of drho over the
 // strip's own nodes.  Returns (job.reduce) whether an own node of this lane had a non-finite or
-// non-positive density.  SUMS: the forces are added into shared.part (job.reduce).
-template <int S, int C, int K, bool GENERAL, int KW = K, bool SUMS = true>
-__device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[K],
-                                            StripShared<typename Codec<S>::real, KW> &shared)
+// non-positive density.  SUMS: the forces are added into shared's slots (job.reduce).
+template <int S, int C, int K, bool GENERAL, int KW = K, bool SUMS = true, typename Shared>
+__device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[K], Shared &shared)
 {
     using P = Cols<S, C>;
     using E = typename Codec<S>::elem;
@@ -472,8 +484,8 @@ __device__ __forceinline__ bool strip_sweep(const StripJob &job, double (&mass)[
                 if (id) body_velocity(shared.body[k][id - 1], c ? x1 : x0, yw, usx, usy);
                 drho[c] = relax_solid(h[c], id != 0, usx, usy, rates, fx, fy);
                 keep(c, h[c]);
-                if (SUMS && job.reduce && row_own && id && (c ? own1 : own0)) {
-                    double *slot = shared.part[k][lane % kForceSlots] + 2 * id;
+                if (SUMS && (Shared::kEveryStep || k == K - 1) && job.reduce && row_own && id && (c ? own1 : own0)) {
+                    double *slot = shared.slot(k, lane) + 2 * id;
                     unsafeAtomicAdd(slot - 1, -double(fx));   // LDS adds that nothing waits for
                     unsafeAtomicAdd(slot, -double(fy));
                 }
