@@ -303,7 +303,8 @@ int vplbm_pool_status(vplbm_pool p, int64_t id, int32_t *state, int64_t *steps_d
    host FP64 fields (nx*ny each; pass NULL to skip).  Releases the request. */
 int vplbm_pool_result(vplbm_pool p, int64_t id, vplbm_obs *out, double *rho, double *ux, double *uy);
 
-/* Device bytes the pool charges a simulation against its budget. */
+/* Device bytes the pool charges a simulation against its budget.  (A request with several bodies over much of
+   its lattice is charged up to 2% more, the sums of their forces, if the budget has so much.) */
 int vplbm_pool_bytes_needed(const vplbm_config *cfg, uint64_t *bytes);
 
 /* Wait for outstanding work, free everything.  NULL-safe. */

@@ -71,10 +71,10 @@ __device__ __forceinline__ void pool_tile_partials(const PoolSim &d, int tile, d
         solid &= ~__ballot(mine);
     }
     __syncthreads();
-    if (threadIdx.x < kRingWidth) {
+    if ((int)threadIdx.x < d.width) {
         double v = 0.0;
         for (int w = 0; w < kBlock2 / 64; w++) v += part[w][threadIdx.x];
-        d.partials[(size_t)tile * kRingWidth + threadIdx.x] = v;
+        d.partials[(size_t)tile * d.width + threadIdx.x] = v;
     }
 }
 
@@ -235,11 +235,11 @@ constexpr int kFoldBlock = 256;
 __global__ __launch_bounds__(kFoldBlock) void pool_fold_kernel(PoolSim *sims, int slot)
 {
     __shared__ double ws[kFoldBlock / 64];
-    const int q = blockIdx.x;
-    const int nt = sims[slot].ntiles;
+    const int q = blockIdx.x, width = sims[slot].width;
+    const int nt = q < width ? sims[slot].ntiles : 0;
     const double *part = sims[slot].partials;
     double v = 0.0;
-    for (int t = threadIdx.x; t < nt; t += kFoldBlock) v += part[(size_t)t * kRingWidth + q];
+    for (int t = threadIdx.x; t < nt; t += kFoldBlock) v += part[(size_t)t * width + q];
     v = wave_sum<false>(v);
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -420,8 +420,9 @@ void set_kernel(PoolSim &d, int kernel, long long done)
     d.launches = (d.body + d.spk - 1) / d.spk + (d.body < d.spl);
 }
 
-// Tiles that a simulation's memory is counted with: those of 64 x 8 nodes, for binary32 64 x 14.  (A
-// strip's blocks are of 8 rows at most: up to twice as many, a 500th part of the simulation's memory.)
+// Tiles that vplbm_pool_bytes_needed counts, with sums of eight bodies each: those of 64 x 8 nodes, for
+// binary32 64 x 14.  There are more blocks of strips than that, but their sums are of the bodies that a
+// request has: only one with several bodies over much of the lattice takes more (charge).
 int count_tiles(const Geom &g, int storage)
 {
     const int th = storage == kF32 ? 14 : kPoolTileH;
@@ -450,6 +451,39 @@ uint64_t bytes_needed(const vplbm_config &c, bool stop = false)
     return 2 * pop + (uint64_t)g.pitch * g.ny + sizeof(BodyParams) * kMaxBodies +
            sizeof(BodyState) * kMaxBodies + (uint64_t)ntiles * kRingWidth * sizeof(double) + residual +
            outlet;
+}
+
+// The kernel that a request is admitted with, what its strips are made of, and the tiles or blocks whose
+// sums it takes memory for.
+struct Parts {
+    int kernel, ntiles, width;
+    std::vector<StripTile> segments;
+};
+Parts parts_of(const Request &r)
+{
+    Parts p;
+    const Geom g = pool_geometry(r.cfg);
+    p.kernel = pool_kernel(r.cfg.storage, g);
+    p.width = 1 + 2 * (int)r.bodies.size();
+    p.ntiles = (g.nx + kPoolTileW - 1) / kPoolTileW * ((g.ny + kPoolTileH - 1) / kPoolTileH);
+    if (p.kernel >= kPoolStrips) {
+        p.segments = pool_segments(r, g, p.kernel);
+        p.ntiles = 0;
+        for (const StripTile &s : p.segments) p.ntiles += segment_blocks(s);
+    }
+    return p;
+}
+
+size_t sum_bytes(int ntiles, int width, bool stop) { return (size_t)ntiles * (width + (stop ? 2 : 0)) * sizeof(double); }
+
+// What a request that needs `need` bytes by the count above is charged: the memory it takes.  One that may
+// run by that count always may: where the difference is all that is missing, alone.
+uint64_t charge(const Request &r, uint64_t need, uint64_t budget)
+{
+    const bool stop = r.tol > 0.0;
+    const Parts p = parts_of(r);
+    const uint64_t counted = sum_bytes(count_tiles(pool_geometry(r.cfg), r.cfg.storage), kRingWidth, stop), taken = sum_bytes(p.ntiles, p.width, stop);
+    return taken <= counted ? need : std::min(need + (taken - counted), budget);
 }
 
 std::mutex g_pool_mu;
@@ -631,27 +665,22 @@ int admit(vplbm_pool p, Request &r, int slot)
     if (!may_admit(st, r.bytes, nodes)) return 0;
     PoolSim d{};
     d.g = pool_geometry(r.cfg);
-    const int kernel = pool_kernel(r.cfg.storage, d.g);
+    Parts parts = parts_of(r);
     d.spl = p->cfg.steps_per_launch;
-    d.tail = kernel >= kPoolStrips ? strips_of(kernel).steps : 0;
-    set_kernel(d, kernel, 0);
-    std::vector<StripTile> segments;
+    d.tail = parts.kernel >= kPoolStrips ? strips_of(parts.kernel).steps : 0;
+    set_kernel(d, parts.kernel, 0);
     d.ntx = (d.g.nx + kPoolTileW - 1) / kPoolTileW;
-    d.ntiles = d.ntx * ((d.g.ny + kPoolTileH - 1) / kPoolTileH);
-    if (d.tail) {
-        segments = pool_segments(r, d.g, kernel);
-        d.ntiles = 0;
-        for (const StripTile &s : segments) d.ntiles += segment_blocks(s);
-    }
+    d.ntiles = parts.ntiles;
+    d.width = parts.width;
     const int conv = r.cfg.bc_xhi == VPLBM_CONVECTIVE ? 1 : 0;
     const size_t pop = (size_t)9 * d.g.plane * elem_bytes(r.cfg.storage);
     struct { void **ptr; size_t n; } allocs[] = {
         {&r.buf[0], pop}, {&r.buf[1], pop}, {(void **)&r.mask, (size_t)d.g.pitch * d.g.ny},
         {(void **)&r.params, sizeof(BodyParams) * kMaxBodies},
         {(void **)&r.state_dev, sizeof(BodyState) * kMaxBodies},
-        {(void **)&r.partials, (size_t)d.ntiles * kRingWidth * sizeof(double)},
+        {(void **)&r.partials, sum_bytes(d.ntiles, d.width, false)},
         {(void **)&r.snap, r.tol > 0.0 ? 2 * (size_t)d.g.nx * d.g.ny * sizeof(double) : 0},
-        {(void **)&r.rpart, r.tol > 0.0 ? (size_t)d.ntiles * 2 * sizeof(double) : 0},
+        {(void **)&r.rpart, r.tol > 0.0 ? sum_bytes(d.ntiles, 0, true) : 0},
         {&r.outlet[0], conv ? 3 * (size_t)d.g.ny * sizeof(double) : 0},
         {&r.outlet[1], conv ? 3 * (size_t)d.g.ny * sizeof(double) : 0},
     };
@@ -709,7 +738,7 @@ int admit(vplbm_pool p, Request &r, int slot)
     HIP_TRY(hipStreamSynchronize(p->stream));
     p->stale = true;
     p->h_sims[slot] = d;
-    p->segments[slot] = std::move(segments);
+    p->segments[slot] = std::move(parts.segments);
     r.slot = slot;
     r.state = VPLBM_RUNNING;
     p->used += r.bytes;
@@ -999,7 +1028,7 @@ int vplbm_pool_submit(vplbm_pool p, const vplbm_config *cfg, const vplbm_body *b
     r.bodies.assign(bodies, bodies + nbodies);
     r.nsteps = nsteps;
     r.keep_fields = keep_fields ? 1 : 0;
-    r.bytes = need;
+    r.bytes = charge(r, need, p->cfg.budget_bytes);
     *id = r.id;
     p->reqs[r.id] = std::move(r);
     p->queue.push_back(*id);
@@ -1021,7 +1050,7 @@ int vplbm_pool_set_stop(vplbm_pool p, int64_t id, double tol, int64_t every)
                     (unsigned long long)need, (unsigned long long)p->cfg.budget_bytes);
     r.tol = tol;
     r.every = every;
-    r.bytes = need;
+    r.bytes = charge(r, need, p->cfg.budget_bytes);
     return VPLBM_OK;
 }
 

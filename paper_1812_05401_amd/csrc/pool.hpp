@@ -15,7 +15,8 @@ struct PoolSim {
     void *buf[2];
     const uint8_t *mask;
     const BodyState *bodies;
-    double *partials;        // [ntiles][kRingWidth] of the final step
+    double *partials;        // [ntiles][width] of the final step
+    int width;               // its mass and two values for each of its bodies
     Geom g;
     NodeParams p;
     int storage;

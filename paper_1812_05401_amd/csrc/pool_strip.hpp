@@ -26,10 +26,10 @@ __device__ __forceinline__ void pool_strip(const StripJob &job, int form, PoolSi
         const double m = wave_sum<wave_sum_dpp<T>()>(mass[KK - 1]);
         if (lane == 0) shared.part[0][0] = double(w) * double(job.y1 - job.y0) + m;
         __syncthreads();
-        if (lane < kRingWidth) {
+        if (lane < sim->width) {
             double v = 0.0;
             for (int q = 0; q < 64; q++) v += shared.part[q][lane];   // fixed order
-            sim->partials[(size_t)block * kRingWidth + lane] = v;
+            sim->partials[(size_t)block * sim->width + lane] = v;
         }
         __syncthreads();
     }
