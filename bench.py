@@ -87,26 +87,6 @@ def measured_traffic(workload, storage, steps_per_launch=1):
     return ent and ent.get("bytes_per_launch")
 
 
-def launch_form(case, tiled):
-    """(kernel, lattice updates per launch) that the library takes for `case`: the rules of
-    strip_f32.hip, strip_f16.hip, strip_f64.hip and patch.hip, else the tiled kernels' `tiled` updates."""
-    st, n = case.storage, case.nx * case.ny
-    wide, fp64 = n >= 5 << 19, st in ("f64", "f32d")
-    strip = {"f32": 6 if wide else 4, "f64": 5, "f32d": 4 if wide else 3, "f16s": 4, "bf16s": 4}.get(st, 0)
-    if n < 800000:
-        strip = 0
-    if st == "f16sr":
-        strip = 3 if n >= 6 << 20 else 0
-    if st == "bf16sr":
-        strip = 3 if n >= 6 << 20 else 4 if n >= 3 << 20 else 0
-    if n <= (799999 if st == "f32" else 650000):
-        return "vplbm::patch_kernel", next((k for m, k in ((24000, 8), (65536, 6), (98304, 5), (150000, 4)) if n <= m), 3 if fp64 else 4)
-    eb = {"f64": 8, "f32": 4, "f32d": 4}.get(st, 2)
-    if strip and case.ny >= strip and 9 * eb * case.ny * ((case.nx + 63) // 64 * 64) < 1 << 32:
-        return "vplbm::strip_kernel", strip
-    return {1: "vplbm::step_kernel", 2: "vplbm::step2_kernel", 3: "vplbm::step3_kernel"}[tiled], tiled
-
-
 def time_workload(case, steps, warmup, storage=None, spl=0):
     """Time `steps` steps of `case` after `warmup`, with at most `spl` steps per launch: 1 creates
     the simulation with VPLBM_TWO_STEP=0, 2 with VPLBM_THREE_STEP=0, 3 with neither strips nor
@@ -134,9 +114,9 @@ def time_workload(case, steps, warmup, storage=None, spl=0):
             else:
                 os.environ[k] = v
     assert sim.stream == stream.cuda_stream
-    tiled = sim.steps_per_launch
-    kernel, spl = launch_form(case, tiled) if spl == 0 else (
-        {1: "vplbm::step_kernel", 2: "vplbm::step2_kernel", 3: "vplbm::step3_kernel"}[tiled], tiled)
+    form, spl = sim.launch_form
+    kernel = {"patches": "vplbm::patch_kernel", "strips": "vplbm::strip_kernel"}.get(
+        form, {1: "vplbm::step_kernel", 2: "vplbm::step2_kernel", 3: "vplbm::step3_kernel"}.get(spl))
     sim.step(warmup)
     torch.cuda.synchronize()
     ev0 = torch.cuda.Event(enable_timing=True)

@@ -216,6 +216,11 @@ int vplbm_stream(vplbm_sim s, void **stream);
    populations (the update of Section 2 per node and step).  EINVAL: bad handle or NULL out. */
 int vplbm_steps_per_launch(vplbm_sim s, int32_t *steps);
 
+/* The kernel that takes this simulation's full launches, and the lattice updates of one of them.  EINVAL:
+   bad handle or NULL output. */
+enum { VPLBM_TILES = 0, VPLBM_STRIPS = 1, VPLBM_PATCHES = 2 };
+int vplbm_launch_form(vplbm_sim s, int32_t *kernel, int32_t *steps);
+
 /* Algorithmic HBM bytes of one lattice update for a storage format: 9 population loads,
    9 population stores and the 1-byte mask. */
 int vplbm_bytes_per_update(int32_t storage, int64_t *bytes);

@@ -87,6 +87,7 @@ SIGNATURES = [
     ("vplbm_residual", C.c_int, [C.c_void_p, _dp]),
     ("vplbm_steps_done", C.c_int, [C.c_void_p, C.POINTER(C.c_int64)]),
     ("vplbm_steps_per_launch", C.c_int, [C.c_void_p, C.POINTER(C.c_int32)]),
+    ("vplbm_launch_form", C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     ("vplbm_stream", C.c_int, [C.c_void_p, C.POINTER(C.c_void_p)]),
     ("vplbm_bytes_per_update", C.c_int, [C.c_int32, C.POINTER(C.c_int64)]),
     ("vplbm_pool_create", C.c_int, [C.POINTER(PoolConfig), C.POINTER(C.c_void_p)]),
@@ -268,6 +269,12 @@ def vplbm_steps_per_launch(h):
     return n.value
 
 
+def vplbm_launch_form(h):
+    kernel, n = C.c_int32(), C.c_int32()
+    check(load().vplbm_launch_form(h, C.byref(kernel), C.byref(n)))
+    return ("tiles", "strips", "patches")[kernel.value], n.value
+
+
 def vplbm_steps_done(h):
     n = C.c_int64()
     check(load().vplbm_steps_done(h, C.byref(n)))
@@ -357,9 +364,14 @@ class Simulation:
 
     @property
     def steps_per_launch(self):
-        """3 for binary32 storage, else 2 (pairs of steps per launch);
+        """Of the tiled kernels: 3 for binary32 storage, else 2 (pairs of steps per launch);
         VPLBM_THREE_STEP=0 caps it at 2 and VPLBM_TWO_STEP=0 at 1."""
         return vplbm_steps_per_launch(self.h)
+
+    @property
+    def launch_form(self):
+        """The kernel that takes the full launches, "tiles", "strips" or "patches", and their steps."""
+        return vplbm_launch_form(self.h)
 
     @property
     def stream(self):

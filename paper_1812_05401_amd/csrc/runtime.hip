@@ -305,20 +305,32 @@ int patch_k(vplbm_sim s)
     return ok ? s->patch->steps : 0;
 }
 
-// Enqueue n steps starting from the state in buf[first_src]: as many as a launch takes (see
-// vplbm_steps_per_launch), and what remains in launches of fewer.  Every launch moves the state to
+// The kernel that takes this simulation's full launches, and their steps.
+struct LaunchForm {
+    int kernel, steps;
+};
+LaunchForm launch_form(vplbm_sim s)
+{
+    if (const int k = patch_k(s)) return {VPLBM_PATCHES, k};
+    if (const int k = strip_k(s)) return {VPLBM_STRIPS, k};
+    return {VPLBM_TILES, three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1};
+}
+
+const char *kernel_name(int kernel) { return kernel == VPLBM_PATCHES ? "patches" : kernel == VPLBM_STRIPS ? "strips" : "tiles"; }
+
+// Enqueue n steps starting from the state in buf[first_src]: as many as a launch takes (launch_form),
+// and what remains in launches of fewer.  Every launch moves the state to
 // the other buffer; *flip is the parity of the number of launches.
 hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int *flip)
 {
-    const int sweep = strip_k(s);
-    const int patch = patch_k(s);
-    const int most = patch ? patch : sweep ? sweep : three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1;
+    const LaunchForm form = launch_form(s);
+    const bool patches = form.kernel == VPLBM_PATCHES, strips = form.kernel == VPLBM_STRIPS;
     const size_t mask_bytes = (size_t)s->g.pitch * s->g.ny;
     int src = first_src;
     int j = 0;
     while (j < n) {
-        int k = n - j < most ? n - j : most;
-        if (k < sweep && k > 2) k = three_step_ok(s) ? 3 : 2;
+        int k = n - j < form.steps ? n - j : form.steps;
+        if (strips && k < form.steps && k > 2) k = three_step_ok(s) ? 3 : 2;
         StepArgs a = step_args(s, src, j);
         hipError_t e = hipSuccess;
         if (s->moving) {
@@ -337,10 +349,10 @@ hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int 
             a.mask_step = mask_bytes;
             a.state_step = kMaxBodies;
         }
-        if (patch) {
+        if (patches) {
             s->patch->launch(a, k, st);
             e = hipGetLastError();
-        } else if (k == sweep) {
+        } else if (strips && k == form.steps) {
             s->shape->launch(a, s->strips, s->nstrips, st);
             e = hipGetLastError();
         } else if (k == 3) e = launch_step3(s->storage, a, st);
@@ -664,9 +676,9 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     track(s, true);
     *out = s;
     host_log("create %p: %dx%d storage %d collision %d, tiles %dx%d x %d rows, %d planes of %d elements, "
-        "non-temporal stores %d, steps per launch %d", (void *)s, g.nx, g.ny, s->storage, cfg->collision,
-        1 << s->ts.bx_log2, s->ts.by, s->ts.rows, 9, g.plane, s->nt_store,
-        three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1);
+        "non-temporal stores %d, %s of %d steps, tiled kernels' steps per launch %d", (void *)s, g.nx, g.ny, s->storage,
+        cfg->collision, 1 << s->ts.bx_log2, s->ts.by, s->ts.rows, 9, g.plane, s->nt_store, kernel_name(launch_form(s).kernel),
+        launch_form(s).steps, three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1);
     return VPLBM_OK;
 }
 
@@ -767,8 +779,8 @@ int vplbm_set_mask(vplbm_sim s, const uint8_t *body_id, const vplbm_body *bodies
         for (uint8_t *m = s->mask_all; m < s->mask; m += mask_bytes)
             HIP_TRY(launch_mask(m, g, s->d_params, s->d_state, nbodies, 0, 0, g.nx, g.ny, s->stream));
     }
-    host_log("set_mask %p: %d bodies, moving %d, steps per launch %d", (void *)s, nbodies,
-             moving ? 1 : 0, three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1);
+    host_log("set_mask %p: %d bodies, moving %d, %s of %d steps, tiled kernels' steps per launch %d", (void *)s, nbodies,
+             moving ? 1 : 0, kernel_name(launch_form(s).kernel), launch_form(s).steps, three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1);
     if (s->steps == 0) {
         HIP_TRY(launch_init(s->storage, step_args(s, s->cur ^ 1, 0), nullptr, nullptr, nullptr, s->cfg.rho0, s->cfg.ux0, s->cfg.uy0, s->stream));
         HIP_TRY(reset_outlet(s));
@@ -983,6 +995,15 @@ int vplbm_steps_per_launch(vplbm_sim s, int32_t *steps)
 {
     if (!valid(s) || !steps) return fail(VPLBM_EINVAL, "invalid handle or NULL output");
     *steps = three_step_ok(s) ? 3 : two_step_ok(s) ? 2 : 1;
+    return VPLBM_OK;
+}
+
+int vplbm_launch_form(vplbm_sim s, int32_t *kernel, int32_t *steps)
+{
+    if (!valid(s) || !kernel || !steps) return fail(VPLBM_EINVAL, "invalid handle or NULL output");
+    const LaunchForm form = launch_form(s);
+    *kernel = form.kernel;
+    *steps = form.steps;
     return VPLBM_OK;
 }
 
