@@ -886,7 +886,7 @@ __global__ __launch_bounds__(kBlock) void mask_kernel(uint8_t *mask, Geom g, con
     mask[y * g.pitch + x] = rasterize_node(x, y, p, s, nb);
 }
 
-// Moving bodies before a launch of a.nsteps (1 to 3) steps: for each step s, the body states at
+// Moving bodies before a launch of a.nsteps (1 to kMaxSteps) steps: for each step s, the body states at
 // time *t_base + t_off + s into a.state[s] and the swept boxes of the moving bodies re-rasterized
 // into a.mask[s], in one launch.  Every workgroup computes the states it needs into LDS (a few
 // FP64 sines per body); workgroup 0 also stores them.  The box nodes of all steps are spread over

@@ -15,8 +15,8 @@ constexpr int kBlock = 256;                      // threads per workgroup (4 wav
 constexpr int kBlock2 = 512;                     // the two-step kernel's workgroup (8 wave64)
 // Per-step reductions go through kSub sub-slots: workgroup b adds its partials into sub-slot
 // b % kSub, so no address takes more than 1/kSub of the atomics (device-scope FP64 atomics to
-// one address serialize).  The next launch's first workgroups (or the fold kernel at observation
-// time) sum the sub-slots in a fixed order into the ring.  Steps use kAccSets sets of sub-slots
+// one address serialize).  Workgroups of the next launch that only reduce (or the fold kernel at
+// observation time) sum the sub-slots in a fixed order into the ring.  Steps use kAccSets sets of sub-slots
 // round-robin, so that a launch of up to kMaxSteps steps can fold the kMaxSteps steps before it
 // while it adds into its own and clears those of the next launch.
 constexpr int kSub = 64;
@@ -111,7 +111,7 @@ hipError_t launch_decode(int storage, const StepArgs &a, double *pop, hipStream_
 hipError_t launch_bodies(const BodyParams *params, BodyState *state, int nbodies,
                          const long long *t_base, int t_off, hipStream_t st);
 
-// Moving bodies before a launch of nsteps (1 to 3) steps, in one launch: for step s of the launch
+// Moving bodies before a launch of nsteps (1 to kMaxSteps) steps, in one launch: for step s of the launch
 // (time *t_base + t_off + s) the body states into state[s] and the swept boxes re-rasterized into
 // mask[s].  box[k] = (x0, y0, w, h) of body k (w = 0: none, e.g. a static body); box_start holds
 // the prefix sums of the box areas (box_start[kMaxBodies] = all of them).  Every box lies inside
@@ -146,7 +146,7 @@ hipError_t launch_residual(int storage, const StepArgs &a, double *snap, double 
 hipError_t launch_momentum_exchange(int storage, const StepArgs &a, double *out, hipStream_t st);
 // Convective outlet: prev = the last column's populations 3, 6, 7 of the state a.src.
 hipError_t launch_outlet_init(int storage, const StepArgs &a, void *prev, hipStream_t st);
-// Sum the sub-slots of steps *t_base - 2 and *t_base - 1 into their ring entries.
+// Sum the sub-slots of steps *t_base - kMaxSteps .. *t_base - 1 into their ring entries.
 hipError_t launch_fold(const StepArgs &a, hipStream_t st);
 // After a restart at step *t_base, all sets cleared: the ring entries of the kMaxSteps steps before into their
 // sets, from which the next folds write them again.

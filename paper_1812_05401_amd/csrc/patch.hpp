@@ -16,7 +16,9 @@
 
 namespace vplbm {
 
-constexpr int kPatchSlots = 16;   // rows of partial sums per step
+// Rows of partial sums per step: a wave's mass is in its own, forces go to row lane % kPatchSlots.  Waves meet
+// there, in no fixed order: the last bits of a force may differ from run to run (populations do not).
+constexpr int kPatchSlots = 16;
 
 // LDS of a patch.  SUMS: with the observables' partial sums.
 template <int S, int TW, int TH, int K, bool SUMS> struct PatchShared {

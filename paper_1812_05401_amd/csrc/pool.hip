@@ -19,11 +19,12 @@
 // and a per-slot fold) that lowers the simulation's target on the device once its
 // velocity change is below the tolerance.
 //
-// Host side.  Between graph replays: retire finished, failed and cancelled simulations (fold,
-// copy results, free memory), admit queued requests first come first served while the memory
-// budget, the slots and the resident-node cap allow, rebuild the tile table.  The graph reads the
-// tables from device memory; it is captured again only when the tile count outgrows its grid or
-// the residual check is switched on or off.
+// Host side.  Between graph replays: retire finished, failed and cancelled simulations (fold), admit
+// queued requests first come first served while the memory budget, the slots and the resident-node cap
+// allow, write the tables anew if anything changed.  The retired simulations' fields go to the host, and
+// their memory back, before admissions where requests wait, else beside the next replay.  The graph reads the
+// tables from device memory; it is captured again when a table outgrows its part of them or fills little
+// of it, when the kernels that residents need change, and when the residual check is switched on or off.
 #include <math.h>
 #include <stddef.h>
 #include <string.h>

@@ -215,8 +215,8 @@ StepArgs step_args(vplbm_sim s, int src, int t_off)
 }
 
 // Body states and the swept part of the mask for the n (1 to kMaxSteps) steps at *t_dev + t_off, ...
-// (moving bodies), in one launch: step s into masks[s] / states[s] (the simulation's own, or for
-// the first step of a two-step launch the other mask and state array).
+// (moving bodies), in one launch: step s into masks[s] / states[s] (for a launch's last step the
+// simulation's own, for those before it the masks and states before those).
 hipError_t place_bodies_n(vplbm_sim s, int t_off, int n, hipStream_t st, uint8_t *const *masks,
                           BodyState *const *states)
 {
