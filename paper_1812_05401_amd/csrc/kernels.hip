@@ -10,6 +10,7 @@
 
 #include "kernels.hpp"
 #include "reduce.hpp"
+#include "step_plan.hpp"
 
 namespace vplbm {
 
@@ -926,7 +927,20 @@ hipError_t launch_bodies(const BodyParams *params, BodyState *state, int nbodies
 
 hipError_t launch_place(const PlaceArgs &a, hipStream_t st)
 {
-    const int total = a.nsteps * a.box_start[kMaxBodies];
+    const int area = a.box_start[kMaxBodies];
+    if (place_steps(a.nsteps, area) < a.nsteps) {   // step by step
+        for (int s = 0; s < a.nsteps; s++) {
+            PlaceArgs one = a;
+            one.nsteps = 1;
+            one.t_off = a.t_off + s;
+            one.mask[0] = a.mask[s];
+            one.state[0] = a.state[s];
+            const hipError_t e = launch_place(one, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    const int total = a.nsteps * area;
     if (total <= 0) {
         // no swept box: only the states (bodies that move without changing the mask)
         place_kernel<<<1, kBlock, 0, st>>>(a);

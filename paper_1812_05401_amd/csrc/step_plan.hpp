@@ -24,4 +24,8 @@ inline StepChunk next_chunk(int64_t remaining, int graph_k)
     return {false, remaining > kDirectChunk ? kDirectChunk : (int)remaining};
 }
 
+// Steps whose swept boxes, `area` nodes in all, one launch of the mask's update may take: the nodes of all
+// its steps are counted in an int.
+inline int place_steps(int steps, int area) { return (long long)steps * area <= 0x7FFFFFFF - (1 << 20) ? steps : 1; }
+
 }  // namespace vplbm
