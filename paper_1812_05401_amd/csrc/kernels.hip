@@ -28,12 +28,11 @@ __global__ __launch_bounds__(kBlock) void step_kernel(StepArgs a)
     __shared__ double wave_acc[kBlock / 64][kRingWidth];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long t = *a.t_base + a.t_off;
-    if ((int)blockIdx.x >= work_blocks(a)) {
-        fold_block(a, t, 1);           // earlier steps' partials are complete (kernel boundary)
-        return;
+    if (a.reduce) {
+        if (lane < kRingWidth) wave_acc[wave][lane] = 0.0;
+        reduction_prologue<kBlock / 64>(a, t, 1);   // earlier steps' partials are complete (kernel boundary)
     }
-    if (a.reduce && lane < kRingWidth) wave_acc[wave][lane] = 0.0;
-    const int tile = xcd_tile(blockIdx.x, work_blocks(a));
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int x = ((tile % a.ntx) << a.bx_log2) + (threadIdx.x & ((1 << a.bx_log2) - 1));
     const int y0 = (tile / a.ntx) * a.by * a.rows + (threadIdx.x >> a.bx_log2);
     const E *__restrict__ src = static_cast<const E *>(a.src);
@@ -101,16 +100,15 @@ __global__ __launch_bounds__(kBlock2) void step2_kernel(StepArgs a)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long t = *a.t_base + a.t_off;
     const Geom &g = a.g;
-    if ((int)blockIdx.x >= work_blocks(a)) {
-        fold_block(a, t, 2);
-        return;
-    }
-    if (a.reduce && lane < kRingWidth) {
-        wave_acc[0][wave][lane] = 0.0;
-        wave_acc[1][wave][lane] = 0.0;
+    if (a.reduce) {
+        if (lane < kRingWidth) {
+            wave_acc[0][wave][lane] = 0.0;
+            wave_acc[1][wave][lane] = 0.0;
+        }
+        reduction_prologue<kBlock2 / 64>(a, t, 2);
     }
     const int ntx = (g.nx + TW - 1) / TW;
-    const int tile = xcd_tile(blockIdx.x, work_blocks(a));
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int x0 = (tile % ntx) * TW, y0 = (tile / ntx) * TH;
     const E *__restrict__ src = static_cast<const E *>(a.src);
     E *__restrict__ dst = static_cast<E *>(a.dst);
@@ -268,14 +266,13 @@ __global__ __launch_bounds__(kBlock2) void step3_kernel(StepArgs a)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long t = *a.t_base + a.t_off;
     const Geom &g = a.g;
-    if ((int)blockIdx.x >= work_blocks(a)) {
-        fold_block(a, t, 3);
-        return;
+    if (a.reduce) {
+        if (lane < kRingWidth)
+            for (int k = 0; k < 3; k++) wave_acc[k][wave][lane] = 0.0;
+        reduction_prologue<kBlock2 / 64>(a, t, 3);
     }
-    if (a.reduce && lane < kRingWidth)
-        for (int k = 0; k < 3; k++) wave_acc[k][wave][lane] = 0.0;
     const int ntx = (g.nx + TW - 1) / TW;
-    const int tile = xcd_tile(blockIdx.x, work_blocks(a));
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int x0 = (tile % ntx) * TW, y0 = (tile / ntx) * TH;
     const E *__restrict__ src = static_cast<const E *>(a.src);
     // the source and destination planes as buffers (the host keeps three-step lattices below 4 GB)
@@ -498,7 +495,7 @@ TileShape tile_shape(int nx, int ny, int elem_bytes)
 
 hipError_t launch_step(int storage, const StepArgs &a, hipStream_t st)
 {
-    const dim3 grid(all_blocks(a, a.ntx * ((a.g.ny + a.by * a.rows - 1) / (a.by * a.rows)))), block(kBlock);
+    const dim3 grid(a.ntx * ((a.g.ny + a.by * a.rows - 1) / (a.by * a.rows))), block(kBlock);
 #define VPLBM_STEP(S)                                                                             \
     (a.nt_store ? step_kernel<S, true><<<grid, block, 0, st>>>(a)                                   \
                 : step_kernel<S, false><<<grid, block, 0, st>>>(a))
@@ -519,7 +516,7 @@ hipError_t launch_step(int storage, const StepArgs &a, hipStream_t st)
 template <int S, int TW, int TH>
 static void launch2(const StepArgs &a, hipStream_t st)
 {
-    const dim3 grid(all_blocks(a, ((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH))), block(kBlock2);
+    const dim3 grid(((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH)), block(kBlock2);
     if (a.outlet.prev) {
         if (a.nt_store) step2_kernel<S, TW, TH, true, true><<<grid, block, 0, st>>>(a);
         else step2_kernel<S, TW, TH, false, true><<<grid, block, 0, st>>>(a);
@@ -535,7 +532,7 @@ hipError_t launch_step3(int storage, const StepArgs &a, hipStream_t st)
 {
     constexpr int TW = 64, TH = 14;
     if (storage != kF32) return hipErrorInvalidValue;
-    const dim3 grid(all_blocks(a, ((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH))), block(kBlock2);
+    const dim3 grid(((a.g.nx + TW - 1) / TW) * ((a.g.ny + TH - 1) / TH)), block(kBlock2);
     if (a.outlet.prev) {   // convective outlet: an instantiation of its own
         if (a.nt_store) step3_kernel<kF32, TW, TH, true, true><<<grid, block, 0, st>>>(a);
         else step3_kernel<kF32, TW, TH, false, true><<<grid, block, 0, st>>>(a);
