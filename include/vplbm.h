@@ -211,8 +211,8 @@ int vplbm_stream(vplbm_sim s, void **stream);
    launches takes launches of one or two steps.  Large lattices, unless one of the two variables
    lowers the figure, take launches of more steps first (a strip sweep, the intermediate steps in
    registers: three to six steps by format and size; VPLBM_STRIP=0 at create turns it off), and the
-   tiled kernels what remains.  Small ones take launches of up to eight steps on patches in LDS, the
-   remainder too (VPLBM_PATCH=0 at create turns that off).  Every launch shape gives bitwise the same
+   tiled kernels what remains.  Small ones take launches of up to eight steps on patches in LDS, and
+   their remainders where the tiled kernels are no faster (VPLBM_PATCH=0 at create turns that off).  Every launch shape gives bitwise the same
    populations (the update of Section 2 per node and step).  EINVAL: bad handle or NULL out. */
 int vplbm_steps_per_launch(vplbm_sim s, int32_t *steps);
 

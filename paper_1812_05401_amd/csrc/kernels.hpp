@@ -75,6 +75,7 @@ struct PatchShape {
     void (*launch)(const StepArgs &a, int nsteps, hipStream_t st);
 };
 const PatchShape *patch_shape(int storage, long long nodes, long long most);
+int patch_least(int storage, long long nodes);   // fewest steps that a launch of patches is taken for
 
 // A form of the strip sweep: columns per lane, steps per launch, waves per SIMD, own columns of a
 // window and the halo beside them, rows of a strip to aim at (strip_slots), and its launch: steps

@@ -62,13 +62,16 @@ template <int S> static const PatchShape *patch_forms(long long nodes)
     return &Patch<S, narrow ? 26 : 20, narrow ? 18 : 17, narrow ? 4 : 3, narrow ? 768 : 512>::shape;
 }
 
-// The largest lattice that patches still win: the two- and three-step kernels (which f32 leaves to the
-// strip sweep) fill the chip at 0.7 million nodes.  us per step, patches and those kernels:
-//   1000 x 601   f32 6.60, 7.65   f64 12.11, 12.75   f32d 10.89, 11.36   f16 9.29, 10.73   f16s 6.80, 8.16
-//   1024 x 768   f32 7.80, 8.61   f64 14.98, 14.42   f32d 13.38, 12.68   f16 11.10, 10.89  f16s 8.17, 8.28
+// The largest lattice that patches still win (a long run): the two- and three-step kernels (which f32 leaves
+// to the strip sweep) fill the chip at 0.7 million nodes, with FP64 arithmetic before that, and stochastic
+// rounding makes the halo's nodes dear, in f16 most.  us per step, patches and those kernels:
+//   640 x 470    f32 4.08, 5.58  f64 6.96, 7.52    f32d 6.06, 6.46    f16 7.10, 7.67   bf16 4.68, 6.35
+//   800 x 500    f32 4.82, 5.57  f64 8.71, 9.12    f32d 7.46, 7.78    f16 8.25, 7.67   bf16 5.65, 6.43
+//   768 x 640    f32 5.62, 6.31  f64 9.90, 10.14   f32d 8.97, 8.91    f16 9.75, 7.84   bf16 6.56, 6.56
+//   840 x 715    f32 6.55, 6.68  f64 11.72, 11.43  f32d 10.56, 10.04  f16s 6.72, 7.54  bf16 7.71, 8.34
 const PatchShape *patch_shape(int storage, long long nodes, long long most)
 {
-    if (most < 0) most = storage == kF32 ? 799999 : 650000;
+    if (most < 0) most = storage == kF32 ? 799999 : storage == kF64 ? 550000 : storage == kF32D ? 450000 : storage == kF16SR ? 350000 : 650000;
     if (nodes > most) return nullptr;
     switch (storage) {
     case kF64: return patch_forms<kF64>(nodes);
@@ -80,6 +83,23 @@ const PatchShape *patch_shape(int storage, long long nodes, long long most)
     case kBF16SR: return patch_forms<kBF16SR>(nodes);
     }
     return nullptr;
+}
+
+// What remains of a call takes the one- and two-step kernels where those are faster: a patch loads and
+// computes its halo for any number of steps.  us per launch of one step, patches and tiles:
+//   200 x 200    f32 6.71, 7.23   f64 7.68, 8.45    f16 7.20, 7.38
+//   256 x 256    f32 8.80, 7.37   f64 9.92, 8.74    f16 9.08, 7.41
+//   768 x 640    f32 13.8, 10.3   f64 20.0, 16.5    bf16 14.0, 10.1
+// and of two (of three, patches are faster or within 2%):
+//   320 x 192    f32 9.4, 12.6    f64 10.9, 11.6   f32d 10.3, 10.9   f16 10.1, 14.6   bf16 9.8, 13.0
+//   384 x 256    f32 8.6, 13.5    f64 12.3, 12.0   f32d 11.4, 11.2   f16 10.9, 15.8   bf16 8.9, 14.1
+//   512 x 400    f32 10.7, 14.2   f64 15.9, 14.6   f32d 13.9, 13.3   f16 15.2, 16.2   bf16 11.5, 14.5
+//   640 x 470    f32 13.4, 14.3   f64 18.7, 17.6   f32d 16.5, 15.3   f16 19.7, 17.7   bf16 14.3, 15.0
+//   800 x 500    f32 15.6, 15.2   f64 22.8, 20.3   f32d 19.5, 17.8   f16s 16.0, 14.0  bf16 17.3, 15.0
+int patch_least(int storage, long long nodes)
+{
+    const long long two = storage == kF64 || storage == kF32D ? 90000 : storage == kF16SR ? 250000 : 350000;
+    return nodes > two ? 3 : nodes > 50000 ? 2 : 1;
 }
 
 }  // namespace vplbm

@@ -155,7 +155,8 @@ struct vplbm_sim_s {
     StripTile *strips = nullptr;
     std::vector<StripTile> strip_list;
     int nstrips = 0, strip_slots = 0;    // entries; strips that a plan aims at
-    const PatchShape *patch = nullptr;   // form of the patch kernel, if the lattice is small
+    const PatchShape *patch = nullptr;   // form of the patch kernel, if the lattice is small,
+    int patch_least = 1;                 //   and the fewest steps of a launch that it takes
     int64_t steps = 0;
     bool unstable = false;
     NodeParams params{};
@@ -331,6 +332,7 @@ hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int 
     while (j < n) {
         int k = n - j < form.steps ? n - j : form.steps;
         if (strips && k < form.steps && k > 2) k = three_step_ok(s) ? 3 : 2;
+        const bool tiles = patches ? k < s->patch_least : strips ? k < form.steps : true;
         StepArgs a = step_args(s, src, j);
         hipError_t e = hipSuccess;
         if (s->moving) {
@@ -349,10 +351,10 @@ hipError_t enqueue_steps(vplbm_sim s, int first_src, int n, hipStream_t st, int 
             a.mask_step = mask_bytes;
             a.state_step = kMaxBodies;
         }
-        if (patches) {
+        if (!tiles && patches) {
             s->patch->launch(a, k, st);
             e = hipGetLastError();
-        } else if (strips && k == form.steps) {
+        } else if (!tiles) {
             s->shape->launch(a, s->strips, s->nstrips, st);
             e = hipGetLastError();
         } else if (k == 3) e = launch_step3(s->storage, a, st);
@@ -588,6 +590,7 @@ int vplbm_create(const vplbm_config *cfg, vplbm_sim *out)
     long long patch_most = -1;
     if (const char *e = getenv("VPLBM_PATCH")) patch_most = atoll(e);   // tuning: largest lattice in nodes, 0: none
     s->patch = patch_shape(cfg->storage, (long long)g.nx * g.ny, patch_most);
+    s->patch_least = patch_least(cfg->storage, (long long)g.nx * g.ny);
     s->graph_k = graph_chunk(s->patch ? s->patch->steps : s->shape ? s->shape->steps : 1);
     s->ts = tile_shape(g.nx, g.ny, elem_bytes(cfg->storage));
 
