@@ -397,12 +397,12 @@ Geom pool_geometry(const vplbm_config &c)
     return g;
 }
 
-// The kernel for a simulation.  The strip sweep needs the planes within its 32-bit offsets and a row of
-// the lattice for every step.
-int pool_kernel(int storage, const Geom &g)
+// The kernel for a simulation in replays of spl steps.  The strip sweep needs the planes within its 32-bit
+// offsets and a row of the lattice for every step.
+int pool_kernel(int storage, const Geom &g, int spl)
 {
     const PoolStrips *strips = pool_strips(storage);
-    if (strips && 9ull * (unsigned long long)g.plane * elem_bytes(storage) <= 0xFFFFFFFFull && g.ny >= strips->steps) return kPoolStrips + storage;
+    if (strips && spl >= pool_least(storage) && 9ull * (unsigned long long)g.plane * elem_bytes(storage) <= 0xFFFFFFFFull && g.ny >= strips->steps) return kPoolStrips + storage;
     return storage == kF64 || storage == kF32D ? kPoolTiles64 : kPoolTiles32;
 }
 
@@ -460,11 +460,11 @@ struct Parts {
     int kernel, ntiles, width;
     std::vector<StripTile> segments;
 };
-Parts parts_of(const Request &r)
+Parts parts_of(const Request &r, int spl)
 {
     Parts p;
     const Geom g = pool_geometry(r.cfg);
-    p.kernel = pool_kernel(r.cfg.storage, g);
+    p.kernel = pool_kernel(r.cfg.storage, g, spl);
     p.width = 1 + 2 * (int)r.bodies.size();
     p.ntiles = (g.nx + kPoolTileW - 1) / kPoolTileW * ((g.ny + kPoolTileH - 1) / kPoolTileH);
     if (p.kernel >= kPoolStrips) {
@@ -479,12 +479,12 @@ size_t sum_bytes(int ntiles, int width, bool stop) { return (size_t)ntiles * (wi
 
 // What a request that needs `need` bytes by the count above is charged: the memory it takes.  One that may
 // run by that count always may: where the difference is all that is missing, alone.
-uint64_t charge(const Request &r, uint64_t need, uint64_t budget)
+uint64_t charge(const Request &r, uint64_t need, const vplbm_pool_config &cfg)
 {
     const bool stop = r.tol > 0.0;
-    const Parts p = parts_of(r);
+    const Parts p = parts_of(r, cfg.steps_per_launch);
     const uint64_t counted = sum_bytes(count_tiles(pool_geometry(r.cfg), r.cfg.storage), kRingWidth, stop), taken = sum_bytes(p.ntiles, p.width, stop);
-    return taken <= counted ? need : std::min(need + (taken - counted), budget);
+    return taken <= counted ? need : std::min(need + (taken - counted), cfg.budget_bytes);
 }
 
 std::mutex g_pool_mu;
@@ -666,7 +666,7 @@ int admit(vplbm_pool p, Request &r, int slot)
     if (!may_admit(st, r.bytes, nodes)) return 0;
     PoolSim d{};
     d.g = pool_geometry(r.cfg);
-    Parts parts = parts_of(r);
+    Parts parts = parts_of(r, p->cfg.steps_per_launch);
     d.spl = p->cfg.steps_per_launch;
     d.tail = parts.kernel >= kPoolStrips ? strips_of(parts.kernel).steps : 0;
     set_kernel(d, parts.kernel, 0);
@@ -1029,7 +1029,7 @@ int vplbm_pool_submit(vplbm_pool p, const vplbm_config *cfg, const vplbm_body *b
     r.bodies.assign(bodies, bodies + nbodies);
     r.nsteps = nsteps;
     r.keep_fields = keep_fields ? 1 : 0;
-    r.bytes = charge(r, need, p->cfg.budget_bytes);
+    r.bytes = charge(r, need, p->cfg);
     *id = r.id;
     p->reqs[r.id] = std::move(r);
     p->queue.push_back(*id);
@@ -1051,7 +1051,7 @@ int vplbm_pool_set_stop(vplbm_pool p, int64_t id, double tol, int64_t every)
                     (unsigned long long)need, (unsigned long long)p->cfg.budget_bytes);
     r.tol = tol;
     r.every = every;
-    r.bytes = charge(r, need, p->cfg.budget_bytes);
+    r.bytes = charge(r, need, p->cfg);
     return VPLBM_OK;
 }
 

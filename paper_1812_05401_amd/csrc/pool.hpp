@@ -89,6 +89,7 @@ struct PoolPatches {
     hipError_t (*launch)(PoolLaunch a, int steps, int grid, hipStream_t st);
 };
 const PoolPatches &pool_patches(int kernel);
+int pool_least(int storage);       // fewest steps of a replay for which strips are taken
 int pool_choose(int storage, long long nodes);   // kernel for a format that has strips, with so many nodes resident
 
 // A replay of spl steps is main launches, spk steps each and what remains last, and a tail launch of

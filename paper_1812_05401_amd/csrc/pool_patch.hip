@@ -78,4 +78,10 @@ int pool_choose(int storage, long long nodes)
     return nodes <= tiles ? kPoolTiles32 : kPoolStrips + storage;
 }
 
+// A strip that takes one step of its three to five still has a window and rows for all of them.  us per
+// replay of one and two steps, 14 simulations of 800 x 800, strips and two-step tiles: f32 256, 262 and 180,
+// 226 (three: 265 in strips); f64 379, 388 and 298, 375, but of four simulations two steps 130 and 138; f32d
+// 257, 271 and 216, 302; f16s 151, 159 and 161, 216; bf16sr 147, 166 and 164, 231; f16sr 150, 179 and 167, 239.
+int pool_least(int storage) { return storage == kF32 ? 3 : storage == kF64 || storage == kF32D ? 2 : 1; }
+
 }  // namespace vplbm
