@@ -40,16 +40,18 @@ inline std::vector<StripTile> strip_segments(const StripPlan &p)
         }
         // rows whose strip rows may see a solid node
         std::fill(solid.begin(), solid.end(), 0);
+        bool clear = true;
         for (int b = 0; b < p.nbox; b++) {
             const int *q = p.box[b];
             if (q[0] > last || q[0] + q[2] <= first) continue;
+            clear = false;
             for (int y = q[1] - reach; y < q[1] + q[3] + reach; y++) {
                 if (y >= 0 && y < p.ny) solid[y] = 1;
                 else if (p.yper) solid[((y % p.ny) + p.ny) % p.ny] = 1;
             }
         }
         for (int y = 0; y < p.ny;) {
-            int e = y + 1;
+            int e = clear ? p.ny : y + 1;
             while (e < p.ny && solid[e] == solid[y]) e++;
             segs.push_back({x0, y, e, solid[y] ? kMasked : kPlain});
             y = e;
@@ -90,15 +92,19 @@ inline std::vector<StripTile> plan_strips(const StripPlan &p, int slots)
         }
         return n;
     });
-    std::vector<StripTile> out;
-    for (const StripTile &s : segs) {
-        const int r = strip_rows(t, s.form, p.steps), h = s.y1 - s.y0, n = (h + r - 1) / r;
-        for (int i = 0; i < n; i++)
-            out.push_back({s.x0, s.y0 + (int)((long long)h * i / n), s.y0 + (int)((long long)h * (i + 1) / n), s.form});
-    }
-    std::stable_sort(out.begin(), out.end(), [](const StripTile &a, const StripTile &b) {
-        return a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0;
-    });
+    // f(strip) for every strip, by columns
+    auto each = [&](auto f) {
+        for (const StripTile &s : segs) {
+            const int r = strip_rows(t, s.form, p.steps), h = s.y1 - s.y0, n = (h + r - 1) / r;
+            for (int i = 0; i < n; i++)
+                f(StripTile{s.x0, s.y0 + (int)((long long)h * i / n), s.y0 + (int)((long long)h * (i + 1) / n), s.form});
+        }
+    };
+    std::vector<int> at(p.ny + 1);       // strips that begin below row y: a counting sort by rows
+    each([&](const StripTile &s) { at[s.y0 + 1]++; });
+    for (int y = 0; y < p.ny; y++) at[y + 1] += at[y];
+    std::vector<StripTile> out(at[p.ny]);
+    each([&](const StripTile &s) { out[at[s.y0]++] = s; });
     return out;
 }
 

@@ -1,5 +1,5 @@
 // The strips of random lattices and boxes (plan_strips): every node of every window in exactly one strip, of
-// the form its rows need, and no more strips than strip_entries says.  Prints "ok", or the first fault.
+// the form its rows need, in order of rows and columns, and no more strips than strip_entries says.  Prints "ok", or the first fault.
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -27,6 +27,8 @@ int main()
         const int own = window - 2 * halo;
         bool bad = (int)list.size() > strip_entries(nx, ny, own, 8, slots);
         std::vector<int> seen((size_t)((nx + own - 1) / own) * ny);
+        for (size_t i = 1; i < list.size(); i++)
+            bad |= list[i].y0 < list[i - 1].y0 || (list[i].y0 == list[i - 1].y0 && list[i].x0 <= list[i - 1].x0);
         for (const StripTile &s : list) {
             bad |= s.x0 % own != 0 || s.y0 < 0 || s.y1 <= s.y0 || s.y1 > ny;
             if (bad) break;
